@@ -1,13 +1,11 @@
 // pack.hip -- quantize-and-pack kernels (Sec. III-C, Eq. 20 with the
 // quantizers of Eqs. 4, 21, 22).
 //
-// Activations: fp32 NCHW -> bitplanes [n][h][w][cw][P].  One thread owns one
-// (image, 32-channel word, pixel); consecutive lanes take consecutive pixels,
-// so each of the 32 channel reads of a wave is one contiguous 256-byte run
-// (HBM-bound: 4 bytes read per channel, P/8 bytes written).
+// Activations: fp32 NCHW -> bitplanes [n][h][w][cw][P] (HBM-bound: 4 bytes
+// read per channel, P/8 bytes written).
 //
 // 16-bit inputs: fp32 NCHW -> fp16 [n][h][w][cw * 32] (round to nearest
-// even; channels past c are +0), with the same thread mapping.
+// even; channels past c are +0).
 //
 // Weights: fp32 OIHW -> per-channel scale s_c = mean|W_c| (double, storage
 // order) -> thresholds scaled by s_c -> bitplanes [kh][kw][cw][cout_pad][P],
@@ -18,88 +16,161 @@ namespace qc {
 
 namespace {
 
-template <int BITS>
-__global__ __launch_bounds__(256) void pack_act_kernel(const float* __restrict__ x, int c,
-                                                       int hw, int cwn, int64_t total, Thr t,
-                                                       uint32_t* __restrict__ out) {
-  constexpr int P = planes_of(BITS);
-  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= total) return;
-  const int pix = (int)(tid % hw);
-  const int64_t r = tid / hw;
-  const int cw = (int)(r % cwn);
-  const int64_t b = r / cwn;
-  const int c0 = cw * 32;
-  const int nch = min(32, c - c0);
-  const float* src = x + (b * c + c0) * (int64_t)hw + pix;
-  uint32_t word[P];
-#pragma unroll
-  for (int p = 0; p < P; ++p) word[p] = 0u;
-  if (nch == 32) {
-#pragma unroll 8
-    for (int j = 0; j < 32; ++j) {
-      const uint32_t pl = quant_planes<BITS>(src[(int64_t)j * hw], t);
-#pragma unroll
-      for (int p = 0; p < P; ++p) word[p] |= ((pl >> p) & 1u) << j;
-    }
-  } else {
-    for (int j = 0; j < nch; ++j) {
-      const uint32_t pl = quant_planes<BITS>(src[(int64_t)j * hw], t);
-#pragma unroll
-      for (int p = 0; p < P; ++p) word[p] |= ((pl >> p) & 1u) << j;
-    }
-  }
-  uint32_t* dst = out + ((b * hw + pix) * cwn + cw) * P;
-#pragma unroll
-  for (int p = 0; p < P; ++p) dst[p] = word[p];
+// Channels of a 32-channel word that exist, given how many remain (>= 1).
+__device__ __forceinline__ uint32_t chan_mask(int remaining) {
+  return remaining >= 32 ? 0xFFFFFFFFu : ((1u << remaining) - 1u);
 }
 
-// The same quantizer with the packed words staged in LDS: a block owns 64
-// pixels of one image and every word of them; wave w computes words w,
-// w + 4, ... with lanes along the pixels (each channel read one contiguous
-// 256-byte run), then the block writes the 64 pixels' words as one
-// contiguous run (the per-thread stores of pack_act_kernel land 4 * P bytes
-// apart and write each HBM sector twice).
-constexpr int PACK_PIX = 64;
+// Activations: a unit is one 32-channel word of 64 consecutive pixels (pixels
+// run over all images), computed by one wave with a pixel per lane: each
+// channel is read as one run of 256 bytes, 16 channels in flight before the
+// first compare.  A block holds the words of `sub` x 64 pixels, one wave per
+// unit, in LDS and writes them as one contiguous run.  Channels past 512 (16
+// words) go to further blocks, whose pixels' words are then runs of 64 P bytes.
+// Bound by reading fp32 from HBM; measured on 1 / 2 / 3 bits with inputs not
+// in cache: 256 x 64 x 56 x 56 37.7 / 40.6 / 45.0 us (5.1-5.6 TB/s), 256 x 512
+// x 8 x 8 8.3 / 8.7 / 9.8 us, where waves that looped over whole pixel runs
+// of one image and branched per 3-bit compare took 37.8 / 40.7 / 120.6 and
+// 12.9 / 14.3 / 63.9 us.  Two or four pixels per lane (8- and 16-byte loads)
+// and 8 or 32 channels in flight measured the same or slower.
+// Compares are gathered from the highest channel down, word = 2 word + bit
+// (one v_addc per compare).  With t0 >= 0, x > t0 is the sign of a nonzero
+// level; the one-hot planes are combined per word.
 template <int BITS>
-__global__ __launch_bounds__(256) void pack_act_lds_kernel(const float* __restrict__ x, int c, int hw, int cwn,
-                                                           int chunks, Thr t, uint32_t* __restrict__ out) {
-  constexpr int P = planes_of(BITS);
-  extern __shared__ uint32_t tile[];  // [PACK_PIX][cwn][P]
-  const int b = blockIdx.x / chunks;
-  const int pix0 = (blockIdx.x - b * chunks) * PACK_PIX;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int pix = pix0 + lane;
-  const bool pok = pix < hw;
-  for (int cw = wave; cw < cwn; cw += 4) {
-    const int c0 = cw * 32;
-    const int nch = min(32, c - c0);
-    const float* src = x + ((int64_t)b * c + c0) * hw + (pok ? pix : 0);
-    uint32_t word[P];
+struct WordBits {
+  static constexpr int NC = BITS == 1 ? 1 : (BITS == 2 ? 2 : 4);
+  uint32_t w[NC];
+  __device__ __forceinline__ void clear() {
 #pragma unroll
-    for (int p = 0; p < P; ++p) word[p] = 0u;
-    if (nch == 32) {
-#pragma unroll 8
-      for (int j = 0; j < 32; ++j) {
-        const uint32_t pl = quant_planes<BITS>(src[(int64_t)j * hw], t);
-#pragma unroll
-        for (int p = 0; p < P; ++p) word[p] |= ((pl >> p) & 1u) << j;
-      }
+    for (int i = 0; i < NC; ++i) w[i] = 0u;
+  }
+  __device__ __forceinline__ void push(float x, const Thr& t) {
+    if constexpr (BITS == 1) {
+      w[0] = w[0] + w[0] + (x > 0.0f ? 1u : 0u);
     } else {
-      for (int j = 0; j < nch; ++j) {
-        const uint32_t pl = quant_planes<BITS>(src[(int64_t)j * hw], t);
-#pragma unroll
-        for (int p = 0; p < P; ++p) word[p] |= ((pl >> p) & 1u) << j;
+      const float ax = fabsf(x);
+      w[0] = w[0] + w[0] + (x > t.t0 ? 1u : 0u);
+      w[1] = w[1] + w[1] + (!(ax <= t.t0) ? 1u : 0u);
+      if constexpr (BITS == 3) {
+        w[2] = w[2] + w[2] + (!(ax <= t.t1) ? 1u : 0u);
+        w[3] = w[3] + w[3] + (!(ax <= t.t2) ? 1u : 0u);
       }
     }
+  }
+  // plane words of the channels in `valid`
+  __device__ __forceinline__ void planes(uint32_t valid, uint32_t* pl) const {
+    pl[0] = w[0] & valid;
+    if constexpr (BITS == 2) pl[1] = w[1] & valid;
+    if constexpr (BITS == 3) {
+      pl[1] = w[3] & valid;
+      pl[2] = w[2] & ~w[3] & valid;
+      pl[3] = w[1] & ~w[2] & valid;
+    }
+  }
+};
+
+// LDS word of packed word i of the block's run: one spare word per 32 keeps
+// lanes whose pixels lie a multiple of 32 words apart in different banks.
+__device__ __forceinline__ int tile_slot(int i) { return i + (i >> 5); }
+
+constexpr int PACK_GROUP = 16;  // words per pixel of a block
+
+template <int BITS>
+__global__ __launch_bounds__(1024) void pack_act_lds_kernel(const float* __restrict__ x, int c, int hw, int cwn,
+                                                            int groups, int npix, int sub, Thr t, int vec_out,
+                                                            uint32_t* __restrict__ out) {
+  constexpr int P = planes_of(BITS);
+  extern __shared__ uint32_t tile[];  // [sub * 64][gw][P], padded by tile_slot
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int pb = groups == 1 ? blockIdx.x : blockIdx.x / groups;
+  const int cw0 = (blockIdx.x - pb * groups) * PACK_GROUP;
+  const int gw = min(cwn - cw0, PACK_GROUP);  // this block's words per pixel
+  const int pix0 = pb * sub * 64;
+  const int sb = wave / gw, cwl = wave - sb * gw;
+  if (sb < sub) {
+    const int pl0 = sb * 64 + lane;             // pixel within the block's run
+    const int pix = min(pix0 + pl0, npix - 1);  // past the end: the last pixel, never written
+    const int b = (int)((uint32_t)pix / (uint32_t)hw);
+    const int c0 = (cw0 + cwl) * 32, nch = min(32, c - c0);
+    const float* src = x + ((int64_t)b * c + c0) * hw + (pix - b * hw);
+    WordBits<BITS> wb;
+    wb.clear();
+    // NB channels from j0 up, every load issued before the first value is waited for
+    auto run = [&](auto NBC, int j0) __attribute__((always_inline)) {
+      constexpr int NB = decltype(NBC)::value;
+      float v[NB];
 #pragma unroll
-    for (int p = 0; p < P; ++p) tile[(lane * cwn + cw) * P + p] = word[p];
+      for (int j = 0; j < NB; ++j) v[j] = src[(int64_t)min(j0 + j, nch - 1) * hw];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = NB - 1; j >= 0; --j) wb.push(v[j], t);
+    };
+    if (nch == 32) {
+      run(std::integral_constant<int, 16>{}, 16);
+      run(std::integral_constant<int, 16>{}, 0);
+    } else {
+      for (int j0 = (nch - 1) & ~3; j0 >= 0; j0 -= 4) run(std::integral_constant<int, 4>{}, j0);
+    }
+    uint32_t pl[P];
+    wb.planes(chan_mask(nch), pl);
+#pragma unroll
+    for (int p = 0; p < P; ++p) tile[tile_slot((pl0 * gw + cwl) * P + p)] = pl[p];
   }
   __syncthreads();
-  const int npix = min(PACK_PIX, hw - pix0);
-  const int nwords = npix * cwn * P;
-  uint32_t* dst = out + ((int64_t)b * hw + pix0) * cwn * P;
-  for (int i = threadIdx.x; i < nwords; i += 256) dst[i] = tile[i];
+  const int nwords = min(sub * 64, npix - pix0) * gw * P;
+  if (groups > 1) {
+    uint32_t* dst = out + ((int64_t)pix0 * cwn + cw0) * P;
+    for (int i = threadIdx.x; i < nwords; i += blockDim.x) {
+      const int px = i / (gw * P);
+      dst[(int64_t)px * cwn * P + (i - px * gw * P)] = tile[tile_slot(i)];
+    }
+    return;
+  }
+  uint32_t* dst = out + (int64_t)pix0 * cwn * P;
+  int done = 0;
+  if (vec_out) {
+    for (int i = threadIdx.x * 4; i + 3 < nwords; i += blockDim.x * 4) {
+      const uint32_t* s = tile + tile_slot(i);
+      *reinterpret_cast<uint4*>(dst + i) = make_uint4(s[0], s[1], s[2], s[3]);
+    }
+    done = nwords & ~3;
+  }
+  for (int i = done + threadIdx.x; i < nwords; i += blockDim.x) dst[i] = tile[tile_slot(i)];
+}
+
+// The same for maps of a few pixels (fully connected inputs): lanes along the
+// channels, a plane's two words of a 64-channel unit are one wave ballot.  A
+// wave takes U units.  (A unit count past 2^32 would need over 500 GB of x.)
+template <int BITS>
+__global__ __launch_bounds__(256) void pack_act_chan_kernel(const float* __restrict__ x, int c, int hw, int cwn,
+                                                            uint32_t units, Thr t, uint32_t* __restrict__ out) {
+  constexpr int P = planes_of(BITS), U = 4;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t pairs = (cwn + 1) / 2;
+  const uint32_t u0 = (blockIdx.x * 4 + wave) * U;
+  float v[U];
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    const uint32_t u = min(u0 + k, units - 1);
+    const uint32_t pix = u / pairs, b = pix / (uint32_t)hw;
+    const int ch = min((int)(u - pix * pairs) * 64 + lane, c - 1);
+    v[k] = x[((int64_t)b * c + ch) * hw + (pix - b * hw)];
+  }
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    const uint32_t u = u0 + k;
+    if (u >= units) break;
+    const uint32_t pix = u / pairs;
+    const int pr = (int)(u - pix * pairs);
+    uint64_t bl[P];
+    plane_ballots<BITS>(v[k], pr * 64 + lane < c, t, bl);
+    const int cw = 2 * pr + lane;
+    if (lane < 2 && cw < cwn) {
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+        out[((int64_t)pix * cwn + cw) * P + p] = lane ? (uint32_t)(bl[p] >> 32) : (uint32_t)bl[p];
+    }
+  }
 }
 
 __global__ __launch_bounds__(256) void pack_act_f16_kernel(const float* __restrict__ x, int c, int hw, int cwn,
@@ -129,6 +200,53 @@ __global__ __launch_bounds__(256) void pack_act_f16_kernel(const float* __restri
   uint4* dst = reinterpret_cast<uint4*>(out + ((b * hw + pix) * cwn + cw) * 16);
 #pragma unroll
   for (int q = 0; q < 4; ++q) dst[q] = make_uint4(h[4 * q], h[4 * q + 1], h[4 * q + 2], h[4 * q + 3]);
+}
+
+// The same through LDS: a block owns 64 consecutive pixels (over all images)
+// x up to F16_GROUP words, one wave per word with all its channels' loads in
+// flight, and writes each pixel's words as one run.  The direct kernel above
+// stores 16 bytes per lane 64 bytes and more apart.  Bound by HBM: 256 x 128 x
+// 32 x 32 46.1 -> 38.9 us (5.2 TB/s read + write), 256 x 64 x 56 x 56 66.1 ->
+// 56.4 us; 4 x 128 x 32 x 32, too few blocks, 3.0 -> 3.7 us.
+constexpr int F16_GROUP = 8;
+__global__ __launch_bounds__(512) void pack_act_f16_lds_kernel(const float* __restrict__ x, int c, int hw, int cwn,
+                                                               int groups, int npix, uint4* __restrict__ out) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t tile[];  // [64][16 gw + 4]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int pb = groups == 1 ? blockIdx.x : blockIdx.x / groups;
+  const int cw0 = (blockIdx.x - pb * groups) * F16_GROUP;
+  const int gw = min(cwn - cw0, F16_GROUP);
+  const int pitch = gw * 16 + 4;  // 4 words of padding: lanes' 16-byte writes fall in different banks
+  const int pix0 = pb * 64;
+  if (wave < gw) {
+    const int pix = min(pix0 + lane, npix - 1);
+    const int b = (int)((uint32_t)pix / (uint32_t)hw);
+    const int c0 = (cw0 + wave) * 32, nch = min(32, c - c0);
+    const float* src = x + ((int64_t)b * c + c0) * hw + (pix - b * hw);
+    float v[32];
+#pragma unroll
+    for (int j = 0; j < 32; ++j) v[j] = src[(int64_t)min(j, nch - 1) * hw];
+    __builtin_amdgcn_sched_barrier(0);  // every load is issued before the first value is waited for
+    uint4* dst = reinterpret_cast<uint4*>(tile + lane * pitch + wave * 16);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint32_t h[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = 8 * q + 2 * e;
+        const uint32_t lo = j < nch ? f16_bits(v[j]) : 0u, hi = j + 1 < nch ? f16_bits(v[j + 1]) : 0u;
+        h[e] = lo | (hi << 16);
+      }
+      dst[q] = make_uint4(h[0], h[1], h[2], h[3]);
+    }
+  }
+  __syncthreads();
+  const int row = gw * 4, n4 = min(64, npix - pix0) * row;
+  uint4* dst = out + ((int64_t)pix0 * cwn + cw0) * 4;
+  for (int i = threadIdx.x; i < n4; i += blockDim.x) {
+    const int px = i / row, r = i - px * row;
+    dst[(int64_t)px * cwn * 4 + r] = *reinterpret_cast<const uint4*>(tile + px * pitch + r * 4);
+  }
 }
 
 // s_c = (float)(sum_k |W_ck| / K), the sum in double in storage order.
@@ -205,11 +323,6 @@ __global__ __launch_bounds__(256) void pack_weight_kernel(const float* __restric
   uint32_t* dst = out + tid * P;
 #pragma unroll
   for (int p = 0; p < P; ++p) dst[p] = word[p];
-}
-
-// Channels of a 32-channel word that exist, given how many remain (>= 1).
-__device__ __forceinline__ uint32_t chan_mask(int remaining) {
-  return remaining >= 32 ? 0xFFFFFFFFu : ((1u << remaining) - 1u);
 }
 
 // Matrix-core operand copies of packed weights: one thread per
@@ -325,29 +438,44 @@ __global__ __launch_bounds__(256) void pack_weight_f16_kernel(const float* __res
 
 }  // namespace
 
+// Lanes along the pixels where a wave's 64 pixels span at most five images (a
+// channel is then read in runs of 64 bytes and more), else along the channels
+// (256 x 1024 x 1 x 1 at 1 bit: 2.5 us, with lanes along the pixels 29.7 us).
+bool pack_act_by_pixel(int n, int h, int w) {
+  return (int64_t)h * w >= 16 && (int64_t)n * h * w < ((int64_t)1 << 31) - 1024;
+}
+
 int launch_pack_act(const float* x, int n, int c, int h, int w, int bits, Thr t, uint32_t* out,
                     hipStream_t s) {
   const int hw = h * w;
   const int cwn = ceil_div(c, 32);
-  const int64_t total = (int64_t)n * cwn * hw;
-  if (total == 0) return QCONV_OK;
-  const size_t lds = (size_t)PACK_PIX * cwn * planes_of(bits) * sizeof(uint32_t);
-  if (lds <= 32 * 1024) {
-    const int chunks = ceil_div(hw, PACK_PIX);
-    const dim3 g((unsigned)((int64_t)n * chunks));
-    switch (bits) {
-      case 1: pack_act_lds_kernel<1><<<g, 256, lds, s>>>(x, c, hw, cwn, chunks, t, out); break;
-      case 2: pack_act_lds_kernel<2><<<g, 256, lds, s>>>(x, c, hw, cwn, chunks, t, out); break;
-      default: pack_act_lds_kernel<3><<<g, 256, lds, s>>>(x, c, hw, cwn, chunks, t, out); break;
-    }
+  const int64_t npix = (int64_t)n * hw;
+  if (npix == 0) return QCONV_OK;
+  if (pack_act_by_pixel(n, h, w)) {
+    // waves per block: one per word of 64 pixels while the tensor has fewer
+    // such runs than four per CU, else at least four, and eight where it has
+    // more than eight per CU (256 x 128 x 32 x 32 at 1 bit: 25.9 -> 24.9 us)
+    const int64_t runs = npix / 64;
+    const int sub = runs < 1024 ? 1 : (cwn < 4 ? ceil_div(4, cwn) : (cwn <= 8 && runs >= 2048 ? 2 : 1));
+    const int groups = ceil_div(cwn, PACK_GROUP), gw = cwn < PACK_GROUP ? cwn : PACK_GROUP;
+    const dim3 g((unsigned)((npix + sub * 64 - 1) / (sub * 64) * groups));
+    const int threads = 64 * sub * gw;
+    const size_t words = (size_t)sub * 64 * gw * planes_of(bits);
+    const size_t lds = (words + words / 32) * sizeof(uint32_t);
+    const int vec_out = ((uintptr_t)out & 15u) == 0;
+#define QC_PACK(B) pack_act_lds_kernel<B><<<g, threads, lds, s>>>(x, c, hw, cwn, groups, (int)npix, sub, t, vec_out, out)
+    if (bits == 1) QC_PACK(1);
+    else if (bits == 2) QC_PACK(2);
+    else QC_PACK(3);
+#undef QC_PACK
     return hip_status();
   }
-  // very wide tensors (more than 32 KB of words per 64 pixels): one thread per word
-  const dim3 grid((unsigned)((total + 255) / 256));
+  const uint32_t units = (uint32_t)(npix * ceil_div(cwn, 2));
+  const dim3 grid((units + 15) / 16);
   switch (bits) {
-    case 1: pack_act_kernel<1><<<grid, 256, 0, s>>>(x, c, hw, cwn, total, t, out); break;
-    case 2: pack_act_kernel<2><<<grid, 256, 0, s>>>(x, c, hw, cwn, total, t, out); break;
-    default: pack_act_kernel<3><<<grid, 256, 0, s>>>(x, c, hw, cwn, total, t, out); break;
+    case 1: pack_act_chan_kernel<1><<<grid, 256, 0, s>>>(x, c, hw, cwn, units, t, out); break;
+    case 2: pack_act_chan_kernel<2><<<grid, 256, 0, s>>>(x, c, hw, cwn, units, t, out); break;
+    default: pack_act_chan_kernel<3><<<grid, 256, 0, s>>>(x, c, hw, cwn, units, t, out); break;
   }
   return hip_status();
 }
@@ -355,8 +483,16 @@ int launch_pack_act(const float* x, int n, int c, int h, int w, int bits, Thr t,
 int launch_pack_act_f16(const float* x, int n, int c, int h, int w, uint32_t* out, hipStream_t s) {
   const int hw = h * w;
   const int cwn = ceil_div(c, 32);
-  const int64_t total = (int64_t)n * cwn * hw;
+  const int64_t npix = (int64_t)n * hw, total = npix * cwn;
   if (total == 0) return QCONV_OK;
+  // through LDS where lanes run along the pixels and every CU gets four waves
+  if (pack_act_by_pixel(n, h, w) && total >= 64 * 1024) {
+    const int groups = ceil_div(cwn, F16_GROUP), gw = cwn < F16_GROUP ? cwn : F16_GROUP;
+    const dim3 g((unsigned)((npix + 63) / 64 * groups));
+    pack_act_f16_lds_kernel<<<g, 64 * gw, 64 * (gw * 16 + 4) * sizeof(uint32_t), s>>>(
+        x, c, hw, cwn, groups, (int)npix, reinterpret_cast<uint4*>(out));
+    return hip_status();
+  }
   pack_act_f16_kernel<<<dim3((unsigned)((total + 255) / 256)), 256, 0, s>>>(x, c, hw, cwn, total, out);
   return hip_status();
 }

@@ -1,0 +1,66 @@
+"""Edges of the kernel choices (run with -m gpu): shapes on both sides of each
+rule that picks a kernel or a block shape, against the CPU oracle.  Packed
+levels and integer accumulators are compared bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2003_04296_amd as q
+from paper_2003_04296_amd import synth
+from helpers import tail_bits_zero, unpack_act, unpack_act16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    oracle.lib()
+    q.lib()
+    return torch.device("cuda:0")
+
+
+def _x(seed, shape):
+    x = synth.normal(synth.generator(seed), shape, 1.0)
+    v = torch.tensor([0.0, -0.0, float("nan"), float("inf"), -float("inf"), 0.5, -0.5, 0.125, 0.375, -0.75, 1e-40])
+    flat = x.view(-1)
+    flat[:: max(1, flat.numel() // 97)][: v.numel()] = v[: flat[:: max(1, flat.numel() // 97)].numel()]
+    return x
+
+
+# lanes along the channels (maps below 16 pixels), along the pixels (from 16
+# on), ragged words, more than 16 words per pixel, and 1 / 2 / 4 runs per block
+PACK_SHAPES = [(5, 70, 3, 5), (9, 64, 1, 1), (3, 33, 4, 4), (2, 513, 4, 5), (1, 1000, 9, 8), (2, 36, 15, 13),
+               (66, 64, 32, 32), (131, 100, 32, 32), (66, 20, 32, 31)]
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3])
+@pytest.mark.parametrize("shape", PACK_SHAPES)
+def test_pack_act(dev, bits, shape):
+    n, c, h, w = shape
+    x = _x(31, shape)
+    words = q.packed_act_words(n, c, h, w, bits)
+    want = oracle.quantize(x.numpy(), bits)
+    for off in (0, 1):  # a 16-byte aligned output, and one that is not
+        out = torch.full((words + 8,), 0x5A5A5A5A, dtype=torch.int32, device=dev)
+        q.pack_act(x.to(dev), bits, out=out[off:off + words])
+        got = out.cpu().numpy()
+        np.testing.assert_array_equal(unpack_act(got[off:off + words], n, c, h, w, bits), want)
+        assert tail_bits_zero(got[off:off + words], c, bits)
+        assert (got[:off] == 0x5A5A5A5A).all() and (got[off + words:] == 0x5A5A5A5A).all()
+
+
+# through LDS from 65536 (pixel, word) pairs on (here 2 and 9 words per
+# pixel), directly below
+@pytest.mark.parametrize("shape", [(33, 40, 32, 32), (8, 270, 31, 31), (3, 40, 9, 9)])
+def test_pack_act16(dev, shape):
+    n, c, h, w = shape
+    x = _x(32, shape)
+    got, pad_ok = unpack_act16(q.pack_act(x.to(dev), 16).cpu().numpy(), n, c, h, w)
+    assert pad_ok
+    want = oracle.to_f16(x.numpy()).view(np.uint16)
+    nan = np.isnan(x.numpy())
+    np.testing.assert_array_equal(got.view(np.uint16)[~nan], want[~nan])
+    assert np.isnan(got[nan]).all()
