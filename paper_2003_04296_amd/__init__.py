@@ -124,15 +124,26 @@ def _check(rc: int, what: str) -> int:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# The two lookups behind torch.cuda.current_stream().cuda_stream, without the
+# Stream object (3 us a call, as much as a launch); None where torch lacks them.
+_raw_stream = None
 
 
 def _stream(stream):
-    import torch
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        import torch
 
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        get, dev = (getattr(torch._C, f, None) for f in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        cur = torch.cuda.current_stream
+        cur()  # initialises the device, and raises where there is none
+        _raw_stream = (lambda: get(dev())) if get and dev else (lambda: cur().cuda_stream)
+    return _raw_stream()
 
 
 # threshold values a quantizer of `bits` reads (Eq. 21: one delta; Eq. 22: three)
@@ -179,10 +190,10 @@ def packed_weight_words(cout, cin, kh, kw, bits) -> int:
 def pack_act(x, bits: int, thresholds=None, out=None, stream=None):
     """fp32 NCHW device tensor -> packed bitplanes [n][h][w][cw][P] (int32 view);
     bits = 16: the fp16 channel-last tensor [n][h][w][cw * 32] (int32 view)."""
-    import torch
-
     n, c, h, w = x.shape
     if out is None:
+        import torch
+
         out = torch.empty(packed_act_words(n, c, h, w, bits), dtype=torch.int32, device=x.device)
     t = _host_thr(thresholds, bits, "pack_act")
     _check(lib().qconv_pack_act(_ptr(x), n, c, h, w, bits, t, _ptr(out), _stream(stream)), "qconv_pack_act")
@@ -192,10 +203,10 @@ def pack_act(x, bits: int, thresholds=None, out=None, stream=None):
 def pack_weight(w, bits: int, base_thresholds=None, stream=None, out=None):
     """fp32 OIHW device tensor -> (packed weights, s_c); out = (words, scale)
     reuses existing buffers."""
-    import torch
-
     cout, cin, kh, kw = w.shape
     if out is None:
+        import torch
+
         out = torch.empty(packed_weight_words(cout, cin, kh, kw, bits), dtype=torch.int32, device=w.device)
         scale = torch.empty(cout, dtype=torch.float32, device=w.device)
     else:
@@ -206,12 +217,16 @@ def pack_weight(w, bits: int, base_thresholds=None, stream=None, out=None):
     return out, scale
 
 
+def _empty_like(x):
+    import torch
+
+    return torch.empty_like(x)
+
+
 def aqe_forward(x, bits: int, alpha: float, thresholds=None, scale=None, group_size: int = 0, out=None, stream=None):
     """AQE forward y = alpha h(x) + (1 - alpha) x (device fp32 tensors);
     weights: pass scale (s_c per group) and group_size (values per group)."""
-    import torch
-
-    y = torch.empty_like(x) if out is None else out
+    y = _empty_like(x) if out is None else out
     t = _host_thr(thresholds, bits, "aqe_forward")
     _check(lib().aqe_forward(_ptr(x), x.numel(), bits, float(alpha), t, _ptr(scale), int(group_size), _ptr(y),
                              _stream(stream)), "aqe_forward")
@@ -220,9 +235,7 @@ def aqe_forward(x, bits: int, alpha: float, thresholds=None, scale=None, group_s
 
 def aqe_backward(x, gy, alpha: float, out=None, stream=None):
     """AQE backward gx = 2 alpha gy 1{|x| <= 1}."""
-    import torch
-
-    gx = torch.empty_like(gy) if out is None else out
+    gx = _empty_like(gy) if out is None else out
     _check(lib().aqe_backward(_ptr(x), _ptr(gy), x.numel(), float(alpha), _ptr(gx), _stream(stream)), "aqe_backward")
     return gx
 
@@ -250,23 +263,27 @@ def conv(act_packed, w_packed, n, cin, h, w, cout, k, stride, pad, a_bits, w_bit
          flags=0, scale=None, bn_k=None, bn_b=None, residual=None, out_bits=0, out=None, out_packed=None,
          algo=ALGO_AUTO, stream=None, out_thresholds=None):
     """qconv_forward; allocates the outputs the epilogue needs when not given."""
-    import torch
+    if (out is None and mode != EPI_BN_PACK) or (out_packed is None and mode == EPI_BN_PACK):
+        import torch
 
-    ho, wo = out_size(h, k, stride, pad), out_size(w, k, stride, pad)
-    if flags & EPI_POOL2:
-        ho, wo = ho // 2, wo // 2
-    dev = act_packed.device
-    if out is None and mode != EPI_BN_PACK:
-        dt = torch.int32 if mode == EPI_INT32 else torch.float32
-        out = torch.empty((n, cout, ho, wo), dtype=dt, device=dev)
-    if out_packed is None and mode == EPI_BN_PACK:
-        out_packed = torch.empty(packed_act_words(n, cout, ho, wo, out_bits), dtype=torch.int32, device=dev)
+        ho, wo = out_size(h, k, stride, pad), out_size(w, k, stride, pad)
+        if flags & EPI_POOL2:
+            ho, wo = ho // 2, wo // 2
+        dev = act_packed.device
+        if mode == EPI_BN_PACK:
+            out_packed = torch.empty(packed_act_words(n, cout, ho, wo, out_bits), dtype=torch.int32, device=dev)
+        else:
+            dt = torch.int32 if mode == EPI_INT32 else torch.float32
+            out = torch.empty((n, cout, ho, wo), dtype=dt, device=dev)
     d = qconv_desc(n, cin, h, w, cout, k, k, stride, pad, a_bits, w_bits, algo)
     thr = _host_thr(out_thresholds, out_bits, "conv") if out_thresholds is not None else None  # alive across the call
     e = qconv_epilogue(mode, flags, _ptr(scale), _ptr(bn_k), _ptr(bn_b), _ptr(residual), out_bits,
                        ctypes.cast(thr, ctypes.c_void_p) if thr is not None else None)
-    _check(lib().qconv_forward(ctypes.byref(d), _ptr(act_packed), _ptr(w_packed), ctypes.byref(e), _ptr(out),
-                               _ptr(out_packed), _stream(stream)), "qconv_forward")
+    rc = lib().qconv_forward(ctypes.byref(d), _ptr(act_packed), _ptr(w_packed), ctypes.byref(e), _ptr(out),
+                             _ptr(out_packed), _stream(stream))
+    if rc < 0:
+        out_size(h, k, stride, pad), out_size(w, k, stride, pad)  # an impossible geometry is reported as that
+        raise QconvError(rc, "qconv_forward")
     return out, out_packed
 
 
