@@ -156,7 +156,8 @@ struct MfmaArgs {
   int vec;            // upi % 4 == 0: four consecutive units are one aligned 16-byte run
   int tiles_px, tiles_co;
   int halo_bytes;
-  int ht_needed;      // requantization thresholds reach 1: apply HardTanh before comparing
+  float inv;          // 2^-shift
+  Thr othr;           // requantization thresholds for |z| (HardTanh folded in, thr_unclamped)
   int out_bytes;      // byte size of the unpacked output (buffer-resource bound, < 2^31)
   int buf_bytes;      // LDS bytes of one halo buffer
   int grid;           // blocks launched (each loops over the work items)
@@ -249,7 +250,7 @@ __device__ __forceinline__ void tile_epilogue(const MfmaArgs& m, const AccT& acc
   const ConvArgs& a = m.c;
   constexpr int POUT = OB ? planes_of(OB) : 1;
   const int g = lane >> 5, r32 = lane & 31;
-  const float inv = 1.0f / (float)(1 << a.shift);
+  const float inv = m.inv;
   const int co = co32 + r32;
   const bool cok = co < a.cout;
   const int64_t oplane = (int64_t)m.upi;  // NCHW channel-plane stride of the output
@@ -339,11 +340,9 @@ __device__ __forceinline__ void tile_epilogue(const MfmaArgs& m, const AccT& acc
       uint64_t bl[4][POUT];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        float zz = z[i];
-        if (m.ht_needed) zz = hardtanh(zz);
         int im, ui;
         const bool uok = unit_of(m, img0, u0, t0 + i, &im, &ui);
-        plane_ballots<OB>(zz, uok & cok, a.othr, bl[i]);
+        plane_ballots<OB>(z[i], uok & cok, m.othr, bl[i]);
       }
       constexpr int B = POOL ? 0 : 8 * QQ;
 #pragma unroll
@@ -365,35 +364,83 @@ __device__ __forceinline__ void tile_epilogue(const MfmaArgs& m, const AccT& acc
   }
 }
 
+// Appends four compare results to w, w = 16 w + {z3, z2, z1, z0 compared}:
+// NLE: !(|z| <= t), else z > t (t wave-uniform).  A compare writes its lane
+// mask to a scalar pair and v_addc takes it as carry, w + w + carry: two
+// instructions a bit, and with the four compares first no wait state between
+// a mask's write and its use (as the compiler orders them, a select, an OR
+// and an s_nop follow each compare).
+template <bool NLE>
+__device__ __forceinline__ uint32_t push4(uint32_t w, float z0, float z1, float z2, float z3, float t) {
+  uint64_t m0, m1, m2, m3;
+  if constexpr (NLE)
+    asm("v_cmp_nle_f32_e64 %1, |%8|, %9\n\t"
+        "v_cmp_nle_f32_e64 %2, |%7|, %9\n\t"
+        "v_cmp_nle_f32_e64 %3, |%6|, %9\n\t"
+        "v_cmp_nle_f32_e64 %4, |%5|, %9\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %1\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %4"
+        : "+v"(w), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+        : "v"(z0), "v"(z1), "v"(z2), "v"(z3), "s"(t)
+        : "vcc");
+  else
+    asm("v_cmp_gt_f32_e64 %1, %8, %9\n\t"
+        "v_cmp_gt_f32_e64 %2, %7, %9\n\t"
+        "v_cmp_gt_f32_e64 %3, %6, %9\n\t"
+        "v_cmp_gt_f32_e64 %4, %5, %9\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %1\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %4"
+        : "+v"(w), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+        : "v"(z0), "v"(z1), "v"(z2), "v"(z3), "s"(t)
+        : "vcc");
+  return w;
+}
+
 // Plane bits of Q(HardTanh(z)) for the 16 values a lane holds in the
 // swapped orientation (Eqs. 4, 21, 22; the quantizer's compares): value
 // v = 4q + i goes to bit 8q + i; the caller shifts the words by 4g, masks
-// missing channels and merges the other half of the word.  HT: apply
-// HardTanh first (only when a threshold reaches 1 does it change a result).
-template <int OB, bool HT>
+// missing channels and merges the other half of the word.  t: thresholds for
+// |z| with HardTanh folded in (thr_unclamped), so t0 >= 0 and z > t0 is the
+// sign of a nonzero level.
+template <int OB>
 __device__ __forceinline__ void swap_plane_bits(const float (&zs)[16], const Thr& t, uint32_t* pw) {
+  auto word = [&](auto NLE, float thr) __attribute__((always_inline)) {
+    uint32_t w = 0u;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int pos = 8 * (v / 4) + (v % 4);
-    const float zz = HT ? hardtanh(zs[v]) : zs[v];
-    const uint32_t s = zz > 0.0f ? 1u : 0u;
-    if constexpr (OB == 1) {
-      pw[0] |= s << pos;
-    } else if constexpr (OB == 2) {
-      const uint32_t nz = !(fabsf(zz) <= t.t0) ? 1u : 0u;
-      pw[0] |= (s & nz) << pos;
-      pw[1] |= nz << pos;
-    } else {
-      const float az = fabsf(zz);
-      const uint32_t a1 = !(az <= t.t0) ? 1u : 0u;
-      const uint32_t a2 = !(az <= t.t1) ? 1u : 0u;
-      const uint32_t a3 = !(az <= t.t2) ? 1u : 0u;
-      pw[0] |= (s & a1) << pos;
-      pw[1] |= a3 << pos;
-      pw[2] |= (a2 & ~a3) << pos;
-      pw[3] |= (a1 & ~a2) << pos;
+    for (int q = 3; q >= 0; --q) {
+      w = push4<decltype(NLE)::value>(w, zs[4 * q], zs[4 * q + 1], zs[4 * q + 2], zs[4 * q + 3], thr);
+      if (q) w <<= 4;
     }
+    return w;
+  };
+  const std::false_type gt{};
+  const std::true_type nle{};
+  if constexpr (OB == 1) {
+    pw[0] = word(gt, 0.0f);
+  } else if constexpr (OB == 2) {
+    pw[0] = word(gt, t.t0);
+    pw[1] = word(nle, t.t0);
+  } else {
+    const uint32_t a1 = word(nle, t.t0), a2 = word(nle, t.t1), a3 = word(nle, t.t2);
+    pw[0] = word(gt, t.t0);
+    pw[1] = a3;
+    pw[2] = a2 & ~a3;
+    pw[3] = a1 & ~a2;
   }
+}
+
+// Units of the item at (img0, u0) that exist, counted from its first one, and
+// the index of that one among all output pixels (consecutive units are
+// consecutive output pixels, across images too).
+__device__ __forceinline__ int item_limit(const MfmaArgs& m, int img0, int u0) {
+  return m.ipb == 1 ? m.upi - u0 : min(m.ipb, m.c.n - img0) * m.upi;
+}
+__device__ __forceinline__ int64_t item_pixel(const MfmaArgs& m, int img0, int u0) {
+  return (int64_t)img0 * m.upi + u0;
 }
 
 // Residual values of one tile of the swapped orientation (register
@@ -437,67 +484,84 @@ __device__ __forceinline__ void tile_epilogue_swap(const MfmaArgs& m, const AccT
                                                    int lane, const float (*pre)[16] = nullptr) {
   constexpr int POUT = OB ? planes_of(OB) : 1;
   uint32_t pw[POUT];
-#pragma unroll
-  for (int p = 0; p < POUT; ++p) pw[p] = 0u;
   float zs[16];  // z of the 16 values, for the packed planes
   const ConvArgs& a = m.c;
   const int g = lane >> 5, r32 = lane & 31;
-  const float inv = 1.0f / (float)(1 << a.shift);
-  int img, uu;
-  const bool uok = unit_of(m, img0, u0, 32 * T + r32, &img, &uu);
+  const int t = 32 * T + r32;
+  const bool uok = t < item_limit(m, img0, u0);
   const int cbase = co32 + 4 * g;
-  const int voff = uok ? (int)((((int64_t)img * a.cout + cbase) * m.upi + uu) * 4) : 0x7FFFFFF0;
-  const __amdgpu_buffer_rsrc_t orsrc =
-      __builtin_amdgcn_make_buffer_rsrc(a.out, (short)0, m.out_bytes, 0x00020000);
-  const bool res = KIND == K_BNF32 && (RES == 1 || (RES == 2 && a.residual_on));
-  float rv[16];
-  if (res) {
-    if (pre) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) rv[v] = (*pre)[v];
-    } else {
-      swap_res_load(m, img0, u0, T, co32, lane, rv);
-    }
-  }
   const bool full = co32 + 32 <= a.cout;  // uniform: no channel of the tile is missing
-  const int pstride = m.upi * 4;
+  // f(v, z) for the 16 values; MUL: the accumulator's scale 2^-shift is not 1
+  auto values = [&](auto MUL, auto&& f) __attribute__((always_inline)) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    float4 k4 = make_float4(0.f, 0.f, 0.f, 0.f), b4 = k4;
-    if constexpr (KIND != K_INT32) {
+    for (int q = 0; q < 4; ++q) {
       const int pc = co32 - co_blk + 8 * q + 4 * g;
-      k4 = *reinterpret_cast<const float4*>(prm + pc);
-      b4 = *reinterpret_cast<const float4*>(prm + 128 + pc);
-    }
-    const float kv[4] = {k4.x, k4.y, k4.z, k4.w};
-    const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
+      const float4 k4 = *reinterpret_cast<const float4*>(prm + pc);
+      float4 b4 = make_float4(0.f, 0.f, 0.f, 0.f);
+      if constexpr (KIND != K_SCALE) b4 = *reinterpret_cast<const float4*>(prm + 128 + pc);
+      const float kv[4] = {k4.x, k4.y, k4.z, k4.w};
+      const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int so = (8 * q + i) * pstride;
-      uint32_t bits;
-      float z = 0.0f;
-      if constexpr (KIND == K_INT32) {
-        bits = (uint32_t)acc_i(acc, 4 * q + i);
-      } else {
-        z = acc_f(acc, 4 * q + i) * inv;
-        if constexpr (KIND == K_SCALE) z = kv[i] * z;
-        if constexpr (KIND == K_BNF32 || KIND == K_PACK) z = fmaf(kv[i], z, bv[i]);
-        if constexpr (KIND == K_BNF32) {
-          if (res) z = z + rv[4 * q + i];
-        }
-        bits = __float_as_uint(z);
+      for (int i = 0; i < 4; ++i) {
+        float z = acc_f(acc, 4 * q + i);
+        if constexpr (decltype(MUL)::value) z = z * m.inv;
+        z = KIND == K_SCALE ? kv[i] * z : fmaf(kv[i], z, bv[i]);
+        f(4 * q + i, z);
       }
-      if constexpr (KIND != K_PACK) {
-        if (full || cbase + 8 * q + i < a.cout) __builtin_amdgcn_raw_buffer_store_b32(bits, orsrc, voff, so, 0);
-      }
-      zs[4 * q + i] = z;
     }
+  };
+  if constexpr (KIND == K_PACK) {
+    auto keep = [&](int v, float z) __attribute__((always_inline)) { zs[v] = z; };
+    if (a.shift == 0) values(std::false_type{}, keep);  // uniform
+    else values(std::true_type{}, keep);
+  } else {
+    int img, uu;
+    unit_of(m, img0, u0, t, &img, &uu);
+    const int voff = uok ? (int)((((int64_t)img * a.cout + cbase) * m.upi + uu) * 4) : 0x7FFFFFF0;
+    const __amdgpu_buffer_rsrc_t orsrc =
+        __builtin_amdgcn_make_buffer_rsrc(a.out, (short)0, m.out_bytes, 0x00020000);
+    const int pstride = m.upi * 4;
+    const bool res = KIND == K_BNF32 && (RES == 1 || (RES == 2 && a.residual_on));
+    float rv[16];
+    if (res) {
+      if (pre) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) rv[v] = (*pre)[v];
+      } else {
+        swap_res_load(m, img0, u0, T, co32, lane, rv);
+      }
+    }
+    // FULL: every channel exists, so the stores need no mask of their own
+    auto store_all = [&](auto FULL) __attribute__((always_inline)) {
+      auto put = [&](int v, uint32_t bits) __attribute__((always_inline)) {
+        const int c = 8 * (v / 4) + v % 4;
+        if constexpr (PERM) {
+          const int vo = decltype(FULL)::value || cbase + c < a.cout ? voff : 0x7FFFFFF0;
+          __builtin_amdgcn_raw_buffer_store_b32(bits, orsrc, vo, c * pstride, 0);
+        } else {
+          if (full || cbase + c < a.cout) __builtin_amdgcn_raw_buffer_store_b32(bits, orsrc, voff, c * pstride, 0);
+        }
+      };
+      if constexpr (KIND == K_INT32) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) put(v, (uint32_t)acc_i(acc, v));
+      } else {
+        values(std::true_type{}, [&](int v, float z) __attribute__((always_inline)) {
+          if constexpr (KIND == K_BNF32) {
+            if (res) z = z + rv[v];
+          }
+          put(v, __float_as_uint(z));
+          zs[v] = z;
+        });
+      }
+    };
+    // PERM false (the store-overlapped kernel, which has no registers for two
+    // forms of z): one form with a branch per store
+    if ((PERM || KIND == K_INT32) && full) store_all(std::true_type{});  // uniform
+    else store_all(std::false_type{});
   }
   if constexpr (OB > 0) {
-    if (m.ht_needed)
-      swap_plane_bits<OB, true>(zs, a.othr, pw);
-    else
-      swap_plane_bits<OB, false>(zs, a.othr, pw);
+    swap_plane_bits<OB>(zs, m.othr, pw);
     if (!full) {
       // channels past the last one are 0 in every plane: bit 8q + i holds
       // channel cbase + 8q + i
@@ -525,7 +589,7 @@ __device__ __forceinline__ void tile_epilogue_swap(const MfmaArgs& m, const AccT
       }
     }
     if (g == 0 && uok) {
-      uint32_t* dst = a.out_packed + (((int64_t)img * m.upi + uu) * a.out_cw + (co32 >> 5)) * POUT;
+      uint32_t* dst = a.out_packed + ((item_pixel(m, img0, u0) + t) * a.out_cw + (co32 >> 5)) * POUT;
       store_words<POUT>(dst, pw);
     }
   }
@@ -598,6 +662,60 @@ __device__ __forceinline__ void epilogue(const MfmaArgs& m, const AccT (&acc)[MT
   }
 }
 
+// Packed output of a pooled layer (windows in four registers of a lane, lanes
+// on channels): per tile and window one maximum, one BN and one wave ballot
+// per plane (lanes 0-31 give the 32 channels of window 4g + i of half 0,
+// lanes 32-63 of half 1), moved into lane 8 i_tile + window of a register per
+// plane, so that the MT tiles' words leave in one store per channel tile
+// and no window needs an index of its own.  (One store, one address and the
+// masks per tile had made this epilogue the longest phase of the pooled
+// layers, 235 instructions a tile at 1 bit: 1W1A 256 x 128 x 32 x 32 -> 128
+// pooled 30.6 -> 23.5 us.)
+template <int OB, int MT, int NT, class AccT>
+__device__ __forceinline__ void pool_pack_tiles(const MfmaArgs& m, const AccT (&acc)[MT][NT], int img0, int u0,
+                                                int tile_m0, int co_w, int co_blk, const float* prm, int lane) {
+  constexpr int P = planes_of(OB);
+  const ConvArgs& a = m.c;
+  const float inv = m.inv;
+  const int t = 8 * tile_m0 + lane;
+  const bool uok = lane < 8 * MT && t < item_limit(m, img0, u0);
+  const int64_t pix = item_pixel(m, img0, u0) + t;
+  Unroll<0, NT>::run([&](auto JJ) __attribute__((always_inline)) {
+    constexpr int j = decltype(JJ)::value;
+    const int co32 = co_w + 32 * j;
+    if (co32 >= a.cout) return;  // uniform
+    const float kj = prm[co32 - co_blk + (lane & 31)], bj = prm[128 + co32 - co_blk + (lane & 31)];
+    uint32_t pw[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) pw[p] = 0u;
+    Unroll<0, MT>::run([&](auto II) __attribute__((always_inline)) {
+      constexpr int i = decltype(II)::value, B = 8 * i;
+      uint64_t bl[4][P];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        float v;
+        if constexpr (std::is_same<AccT, v16i>::value)
+          v = (float)max(max(acc[i][j][4 * w], acc[i][j][4 * w + 1]), max(acc[i][j][4 * w + 2], acc[i][j][4 * w + 3]));
+        else
+          v = fmaxf(fmaxf(acc[i][j][4 * w], acc[i][j][4 * w + 1]), fmaxf(acc[i][j][4 * w + 2], acc[i][j][4 * w + 3]));
+        plane_ballots<OB>(fmaf(kj, v * inv, bj), true, m.othr, bl[w]);
+      }
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+        pw[p] = writelanes8<B, B + 1, B + 2, B + 3, B + 4, B + 5, B + 6, B + 7>(
+            pw[p], (uint32_t)bl[0][p], (uint32_t)bl[1][p], (uint32_t)bl[2][p], (uint32_t)bl[3][p],
+            (uint32_t)(bl[0][p] >> 32), (uint32_t)(bl[1][p] >> 32), (uint32_t)(bl[2][p] >> 32),
+            (uint32_t)(bl[3][p] >> 32));
+    });
+    if (co32 + 32 > a.cout) {  // uniform: channels past the last one are 0 in every plane
+      const uint32_t valid = (1u << (a.cout - co32)) - 1u;
+#pragma unroll
+      for (int p = 0; p < P; ++p) pw[p] &= valid;
+    }
+    if (uok) store_words<P>(a.out_packed + (pix * a.out_cw + (co32 >> 5)) * P, pw);
+  });
+}
+
 // The packed and BN outputs of pooled layers (the case of this orientation
 // in networks) run the unrolled tile sequence; other outputs the loop.
 template <int KIND, int POOL, int MT, int NT, class AccT>
@@ -623,7 +741,15 @@ __device__ __forceinline__ void epilogue_mode(const MfmaArgs& m, const AccT (&ac
       epilogue<K_SCALE, 0, POOL, false>(m, acc, img0, u0, tile_m0, co_w, co_blk, prm, lane);
       break;
     case QCONV_EPI_BN_F32: epilogue_ob<K_BNF32, POOL>(m, acc, img0, u0, tile_m0, co_w, co_blk, prm, lane); break;
-    default: epilogue_ob<K_PACK, POOL>(m, acc, img0, u0, tile_m0, co_w, co_blk, prm, lane); break;
+    default:
+      if constexpr (POOL == 1) {
+        if (m.c.out_bits == 1) pool_pack_tiles<1>(m, acc, img0, u0, tile_m0, co_w, co_blk, prm, lane);
+        else if (m.c.out_bits == 2) pool_pack_tiles<2>(m, acc, img0, u0, tile_m0, co_w, co_blk, prm, lane);
+        else pool_pack_tiles<3>(m, acc, img0, u0, tile_m0, co_w, co_blk, prm, lane);
+      } else {
+        epilogue_ob<K_PACK, POOL>(m, acc, img0, u0, tile_m0, co_w, co_blk, prm, lane);
+      }
+      break;
   }
 }
 

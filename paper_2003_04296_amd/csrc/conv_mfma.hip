@@ -123,7 +123,8 @@ bool plan(const ConvArgs& a, int cfg, MfmaArgs* m) {
   m->tiles_co = ceil_div(a.cout, cfg_block_co(cfg));
   if (m->tiles_px < 1 || m->tiles_co < 1) return false;  // never an empty launch
   m->halo_bytes = m->slot_pix * m->pix_bytes * m->ipb;
-  m->ht_needed = a.out_packed && hardtanh_needed(a.out_bits, a.othr);
+  m->inv = 1.0f / (float)(1 << a.shift);
+  m->othr = thr_unclamped(a.othr);
   const int64_t ab = (int64_t)a.n * a.h * a.w * a.cw * act_words(a.a_bits) * 4;
   m->act_bytes = ab < ((int64_t)1 << 31) ? (int)ab : 0;
   const int64_t ob = (int64_t)a.n * a.cout * m->upi * 4;

@@ -64,3 +64,28 @@ def test_pack_act16(dev, shape):
     nan = np.isnan(x.numpy())
     np.testing.assert_array_equal(got.view(np.uint16)[~nan], want[~nan])
     assert np.isnan(got[nan]).all()
+
+
+# packed outputs of pooled layers on every block shape: 256 rows x 128 and x 64
+# channels and the split-K shape, ragged channels, 255 windows an image
+@pytest.mark.parametrize("bits", [1, 2, 3])
+@pytest.mark.parametrize("n, cout, cfg", [(130, 100, 0), (130, 48, 1), (3, 100, 2)])
+def test_pooled_packed_output(dev, n, cout, cfg, bits):
+    cin, h, w = 40, 30, 34
+    g = synth.generator(34)
+    x = synth.normal(g, (n, cin, h, w), 1.0)
+    wt = synth.normal(g, (cout, cin, 3, 3), 2.0 / (9 * cin))
+    kk, bb = synth.uniform(g, (cout,), 0.01, 0.05), synth.normal(g, (cout,), 0.1)
+    name = q.kernel_name(n, cin, h, w, cout, 3, 1, 1, bits, bits, mode=q.EPI_BN_PACK, flags=q.EPI_POOL2,
+                         out_bits=bits, packed_out=True)
+    assert int(name.split("<")[1].split(",")[2]) == cfg, name
+    wq, _ = q.pack_weight(wt.to(dev), bits)
+    _, got = q.conv(q.pack_act(x.to(dev), bits), wq, n, cin, h, w, cout, 3, 1, 1, bits, bits, mode=q.EPI_BN_PACK,
+                    flags=q.EPI_POOL2, bn_k=kk.to(dev), bn_b=bb.to(dev), out_bits=bits)
+    lw, _ = oracle.quantize_weights(wt.numpy(), bits)
+    acc = oracle.qconv_acc(oracle.quantize(x.numpy(), bits), lw, bits, 1, 1)
+    acc = acc.reshape(n, cout, h // 2, 2, w // 2, 2).max(axis=(3, 5))
+    z = oracle.epi_bn(acc, kk.numpy(), bb.numpy(), 2 * oracle.level_shift(bits))
+    np.testing.assert_array_equal(unpack_act(got.cpu().numpy(), n, cout, h // 2, w // 2, bits),
+                                  oracle.quantize(oracle.hardtanh(z), bits))
+    assert tail_bits_zero(got.cpu().numpy(), cout, bits)
