@@ -405,6 +405,152 @@ __global__ __launch_bounds__(256) void expand_weight_kernel(const uint32_t* __re
   }
 }
 
+// The planes and every operand copy in one pass over the weights: a block
+// owns CO output channels x 64 input channels, whose taps are one contiguous
+// run per output channel.  A wave reads whole runs (row by row, V weights per
+// lane, eight rows in flight), so a lane's (channel, tap) places are the same
+// for every row; the plane bits go to LDS as a byte per weight, ordered
+// [output channel][tap][word] with channel 8 b + k of a word in byte b of u32
+// k, so that a thread builds a plane word of one (tap, word, output channel)
+// as the OR of its eight u32, masked and shifted by k.  Lanes run along the
+// output channels there, so every copy leaves in runs of 32 CO bytes.  Bound
+// by HBM (4 bytes read, 3.5 + P / 8 written per weight).  With the scales,
+// 2432 x 512 x 3 x 3 at 2 bits: 27.2 us, where a gather of single weights 36
+// bytes apart (pack_weight_kernel) and a second pass over its planes
+// (expand_weight_kernel) took 69.2; those two remain for kernels of more taps
+// than fit in LDS.
+constexpr int PWT_MAX_TAPS = 25;
+__host__ __device__ constexpr int pwt_pitch(int taps) { return 64 * taps + 16; }  // LDS bytes per output channel
+
+template <int BITS, int CO, int V>
+__global__ __launch_bounds__(256) void pack_weight_tile_kernel(
+    const float* __restrict__ w, int cout, int cin, int taps, FastDiv fd_taps, int cwn, int cop, Thr base,
+    const float* __restrict__ scale, uint32_t* __restrict__ out, uint8_t* __restrict__ w_i8,
+    uint8_t* __restrict__ w_fp4, uint8_t* __restrict__ w_f16) {
+  constexpr int P = planes_of(BITS), R = CO / 4;  // rows per wave
+  extern __shared__ __attribute__((aligned(16))) uint8_t codes[];  // [CO][pitch]
+  __shared__ float thr[3][CO];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int pairs = (cwn + 1) / 2;
+  const int kp = blockIdx.x % pairs, co0 = (blockIdx.x / pairs) * CO;
+  const int c0 = kp * 64, nch = min(64, cin - c0);
+  const int nco = min(CO, cout - co0);  // <= 0: padding rows only
+  const int pitch = pwt_pitch(taps);
+  if (threadIdx.x < CO) {
+    // the same rounding as pack_weight_kernel
+    const double s = (double)scale[min(co0 + (int)threadIdx.x, cout - 1)];
+    thr[0][threadIdx.x] = (float)((double)base.t0 * s);
+    thr[1][threadIdx.x] = (float)((double)base.t1 * s);
+    thr[2][threadIdx.x] = (float)((double)base.t2 * s);
+  }
+  if (nch < 64)  // uniform: channels past the last one are 0 in every plane
+    for (int i = threadIdx.x; i < CO * pitch / 16; i += 256)
+      reinterpret_cast<uint4*>(codes)[i] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  const int len = nch * taps;
+  const float* src = w + ((int64_t)co0 * cin + c0) * taps;
+  const int64_t rs = (int64_t)cin * taps;
+  if (nco > 0) {
+    for (int e0 = 0; e0 < len; e0 += 64 * V) {
+      const int e = e0 + lane * V;
+      const bool ok = e < len;  // V = 4: len is a multiple of 4
+      const int el = ok ? e : 0;
+      float v[R][V];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const float* s = src + min(wave + 4 * r, nco - 1) * rs + el;
+        if constexpr (V == 4) {
+          const float4 f = *reinterpret_cast<const float4*>(s);
+          v[r][0] = f.x;
+          v[r][1] = f.y;
+          v[r][2] = f.z;
+          v[r][3] = f.w;
+        } else {
+          v[r][0] = *s;
+        }
+      }
+      int off[V];
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        const int c = (int)fdiv((uint32_t)(el + i), fd_taps), tap = el + i - c * taps;
+        off[i] = tap * 64 + (c & 32) + (c & 7) * 4 + ((c >> 3) & 3);
+      }
+      if (ok) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int row = wave + 4 * r;
+          const float t0 = thr[0][row], t1 = thr[1][row], t2 = thr[2][row];
+          uint8_t* d = codes + row * pitch;
+#pragma unroll
+          for (int i = 0; i < V; ++i) {
+            // plane bits of a weight (those of quant_planes, without branches)
+            const float x = v[r][i];
+            uint32_t b;
+            if constexpr (BITS == 1) {
+              b = x > 0.0f ? 1u : 0u;
+            } else {
+              const float ax = fabsf(x);
+              b = x > t0 ? 1u : 0u;
+              if constexpr (BITS == 2) b |= !(ax <= t0) ? 2u : 0u;
+              else b |= !(ax <= t2) ? 2u : (!(ax <= t1) ? 4u : (!(ax <= t0) ? 8u : 0u));
+            }
+            d[off[i]] = (uint8_t)b;
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+  for (int u = threadIdx.x; u < 2 * CO * taps; u += 256) {
+    const int col = u & (CO - 1), h = (u / CO) & 1, tap = u / (2 * CO);
+    const int co = co0 + col, cw = 2 * kp + h;
+    const uint4* cp = reinterpret_cast<const uint4*>(codes + col * pitch + tap * 64 + 32 * h);
+    const uint4 x0 = cp[0], x1 = cp[1];
+    const uint32_t x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+    const bool in = col < nco && cw < cwn;
+    const uint32_t valid = in ? chan_mask(cin - cw * 32) : 0u;
+    uint32_t pl[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      uint32_t o = 0u;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) o |= ((x[k] >> p) & 0x01010101u) << k;
+      pl[p] = in ? o : 0u;
+    }
+    uint32_t f4[4];
+    expand_fp4_word<P>(pl, valid, f4);
+    *reinterpret_cast<uint4*>(w_fp4 + (((int64_t)tap * pairs + kp) * cop + co) * 32 + 16 * h) =
+        make_uint4(f4[0], f4[1], f4[2], f4[3]);
+    if (cw >= cwn) continue;
+    const int64_t rec = ((int64_t)tap * cwn + cw) * cop + co;
+#pragma unroll
+    for (int p = 0; p < P; ++p) out[rec * P + p] = pl[p];
+    uint32_t o[8];
+    expand_i8_word<P>(pl, valid, o);
+    uint4* d8 = reinterpret_cast<uint4*>(w_i8 + rec * 32);
+    d8[0] = make_uint4(o[0], o[1], o[2], o[3]);
+    d8[1] = make_uint4(o[4], o[5], o[6], o[7]);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      uint32_t hv[8];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) i8_word_to_f16(o[4 * half + q], &hv[2 * q], &hv[2 * q + 1]);
+      uint4* df = reinterpret_cast<uint4*>(w_f16 + (((int64_t)tap * 2 * cwn + 2 * cw + half) * cop + co) * 32);
+      df[0] = make_uint4(hv[0], hv[1], hv[2], hv[3]);
+      df[1] = make_uint4(hv[4], hv[5], hv[6], hv[7]);
+    }
+  }
+}
+
+template <int BITS, int CO, int V>
+void pack_weight_tiles(const float* w, int cout, int cin, int taps, Thr base, const float* scale, uint32_t* out,
+                       uint8_t* w_i8, uint8_t* w_fp4, uint8_t* w_f16, hipStream_t s) {
+  const int cwn = ceil_div(cin, 32), cop = cout_pad(cout);
+  const dim3 g((unsigned)(ceil_div(cwn, 2) * (cop / CO)));
+  pack_weight_tile_kernel<BITS, CO, V><<<g, 256, (size_t)CO * pwt_pitch(taps), s>>>(
+      w, cout, cin, taps, make_fastdiv((uint32_t)taps), cwn, cop, base, scale, out, w_i8, w_fp4, w_f16);
+}
+
 // 16-bit weights (Table I rows with 1..3-bit inputs and 16-bit weights):
 // fp32 OIHW -> fp16 [kh][kw][2 cw][cout_pad][16 halves], the layout of the
 // fp16 operand copy, rounded to nearest even; channels past cin and padding
@@ -513,18 +659,36 @@ int launch_pack_weight(const float* w, int cout, int cin, int kh, int kw, int bi
   weight_scale_kernel<<<cout, 256, 0, s>>>(w, k, scale);
   const int cwn = ceil_div(cin, 32);
   const int cop = cout_pad(cout);
-  const int64_t total = (int64_t)kh * kw * cwn * cop;
-  const dim3 grid((unsigned)((total + 255) / 256));
+  const int taps = kh * kw;
   Thr b = {base_thr[0], base_thr[1], base_thr[2]};
+  uint8_t* w_i8 = reinterpret_cast<uint8_t*>(out) + wbytes_planes(cout, cin, kh, kw, bits);
+  uint8_t* w_fp4 = w_i8 + wbytes_i8(cout, cin, kh, kw);
+  uint8_t* w_f16 = w_fp4 + wbytes_fp4(cout, cin, kh, kw);
+  if (taps <= PWT_MAX_TAPS) {
+    // 16-byte loads where every run starts on 16 bytes; 32 output channels
+    // per block where that gives every CU two blocks, else 8
+    const bool vec = ((int64_t)cin * taps) % 4 == 0 && ((uintptr_t)w & 15u) == 0;
+    const bool wide = ceil_div(cwn, 2) * (cop / 32) >= 512;
+#define QC_PWT(B)                                                                                              \
+  do {                                                                                                         \
+    if (wide && vec) pack_weight_tiles<B, 32, 4>(w, cout, cin, taps, b, scale, out, w_i8, w_fp4, w_f16, s);    \
+    else if (wide) pack_weight_tiles<B, 32, 1>(w, cout, cin, taps, b, scale, out, w_i8, w_fp4, w_f16, s);      \
+    else if (vec) pack_weight_tiles<B, 8, 4>(w, cout, cin, taps, b, scale, out, w_i8, w_fp4, w_f16, s);        \
+    else pack_weight_tiles<B, 8, 1>(w, cout, cin, taps, b, scale, out, w_i8, w_fp4, w_f16, s);                 \
+  } while (0)
+    if (bits == 1) QC_PWT(1);
+    else if (bits == 2) QC_PWT(2);
+    else QC_PWT(3);
+#undef QC_PWT
+    return hip_status();
+  }
+  const int64_t total = (int64_t)taps * cwn * cop;
+  const dim3 grid((unsigned)((total + 255) / 256));
   switch (bits) {
     case 1: pack_weight_kernel<1><<<grid, 256, 0, s>>>(w, cout, cin, kh, kw, cwn, cop, b, scale, out); break;
     case 2: pack_weight_kernel<2><<<grid, 256, 0, s>>>(w, cout, cin, kh, kw, cwn, cop, b, scale, out); break;
     default: pack_weight_kernel<3><<<grid, 256, 0, s>>>(w, cout, cin, kh, kw, cwn, cop, b, scale, out); break;
   }
-  uint8_t* w_i8 = reinterpret_cast<uint8_t*>(out) + wbytes_planes(cout, cin, kh, kw, bits);
-  uint8_t* w_fp4 = w_i8 + wbytes_i8(cout, cin, kh, kw);
-  uint8_t* w_f16 = w_fp4 + wbytes_fp4(cout, cin, kh, kw);
-  const int taps = kh * kw;
   const int64_t items =
       (int64_t)taps * cwn * cop + (int64_t)taps * ((cwn + 1) / 2) * cop + (int64_t)taps * 2 * cwn * cop;
   const dim3 g2((unsigned)((items + 255) / 256));

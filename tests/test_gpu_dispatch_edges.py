@@ -8,7 +8,7 @@ import torch
 import oracle
 import paper_2003_04296_amd as q
 from paper_2003_04296_amd import synth
-from helpers import tail_bits_zero, unpack_act, unpack_act16
+from helpers import tail_bits_zero, unpack_act, unpack_act16, unpack_weight, weight_copies, weight_copy_f16
 
 pytestmark = pytest.mark.gpu
 
@@ -64,6 +64,29 @@ def test_pack_act16(dev, shape):
     nan = np.isnan(x.numpy())
     np.testing.assert_array_equal(got.view(np.uint16)[~nan], want[~nan])
     assert np.isnan(got[nan]).all()
+
+
+# one pass per 8 or 32 output channels (32 from 512 blocks of those on), with
+# 16- and 4-byte loads, around 64 input channels, at the most taps its LDS
+# holds and past them (the gather)
+@pytest.mark.parametrize("bits", [1, 2, 3])
+@pytest.mark.parametrize("shape", [(9, 64, 3, 3), (130, 63, 3, 3), (33, 65, 2, 2), (2050, 512, 1, 1), (2050, 511, 1, 1),
+                                   (17, 70, 5, 5), (17, 70, 6, 6)])
+def test_pack_weight(dev, bits, shape):
+    cout, cin, kh, kw = shape
+    w = synth.normal(synth.generator(33), shape, 2.0 / (cin * kh * kw))
+    w.view(-1)[:2] = torch.tensor([0.0, -0.0])
+    lv, s = oracle.quantize_weights(w.numpy(), bits)
+    for off in (0, 1):  # 16-byte aligned weights, and weights that are not
+        buf = torch.zeros(w.numel() + 4, device=dev)
+        buf[off:off + w.numel()] = w.reshape(-1).to(dev)
+        words, scale = q.pack_weight(buf[off:off + w.numel()].view(shape), bits)
+        words = words.cpu().numpy()
+        np.testing.assert_array_equal(scale.cpu().numpy(), s)
+        np.testing.assert_array_equal(unpack_weight(words, cout, cin, kh, kw, bits), lv)
+        for copy in weight_copies(words, cout, cin, kh, kw, bits):
+            np.testing.assert_array_equal(copy, lv)
+        np.testing.assert_array_equal(weight_copy_f16(words, cout, cin, kh, kw, bits), lv)
 
 
 # packed outputs of pooled layers on every block shape: 256 rows x 128 and x 64
