@@ -244,6 +244,8 @@ bool use_pp(const MfmaArgs& m, int cfg, int cus) {
 
 using namespace mfma;
 
+bool mfma_is_small(const ConvArgs& a) { return lat_applies(a); }
+
 bool mfma_supports(const ConvArgs& a) {
   if (a.stride > 2 || a.n == 0) return false;
   MfmaArgs m;
@@ -255,7 +257,9 @@ int mfma_kernel_name(const ConvArgs& a, char* buf, int len) {
   const int cfg = pick_cfg(a);
   if (!plan(a, cfg, &m)) return QCONV_EUNSUPPORTED;
   char name[96];
-  if (use_pp(m, cfg, device_cus()))
+  if (lat_applies(a))
+    lat_kernel_name(a, name, (int)sizeof(name));
+  else if (use_pp(m, cfg, device_cus()))
     snprintf(name, sizeof(name), "conv_mfma_pp_kernel<%d, %d, %d, %d>", a.mfma_op, act_words(a.a_bits), cfg,
              a.out_packed ? a.out_bits : 0);
   else
@@ -269,6 +273,7 @@ int launch_conv_mfma(const ConvArgs& a, hipStream_t s) {
   MfmaArgs m;
   const int cfg = pick_cfg(a);
   if (!plan(a, cfg, &m)) return QCONV_EUNSUPPORTED;
+  if (lat_applies(a)) return launch_conv_lat(a, s);
   const int pa = act_words(a.a_bits);
   if (a.mfma_op == OP_F16) {
     if (pa == 16) return launch_mfma_f16_p16(m, cfg, s);

@@ -63,13 +63,6 @@ __device__ __forceinline__ float hardtanh(float v) {
   return v;
 }
 
-// The bitplane compares may take z itself instead of HardTanh(z) unless a
-// threshold reaches 1: below 1, |HardTanh(z)| <= t exactly when |z| <= t, and
-// the sign is kept.
-inline bool hardtanh_needed(int bits, Thr t) {
-  return (bits == 2 && t.t0 >= 1.0f) || (bits == 3 && t.t2 >= 1.0f);
-}
-
 // n / d by a multiply-high, exact whenever n * d < 2^32 (checked on the host
 // against the largest dividend of each use).
 struct FastDiv {
@@ -307,6 +300,9 @@ int launch_conv_xnor(const ConvArgs& a, hipStream_t s);
 int xnor_kernel_name(const ConvArgs& a, char* buf, int len);
 int launch_conv_mfma(const ConvArgs& a, hipStream_t s);
 bool mfma_supports(const ConvArgs& a);
+// Whether the matrix-core layer has few output tiles (conv_lat.h): AUTO then
+// takes it whatever the contraction's size.
+bool mfma_is_small(const ConvArgs& a);
 // Name of the kernel instantiation each launcher would run (template
 // arguments as the profiler prints them); returns the name's length.
 int bitplane_kernel_name(const ConvArgs& a, char* buf, int len);

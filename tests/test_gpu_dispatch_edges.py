@@ -92,7 +92,7 @@ def test_pack_weight(dev, bits, shape):
 # packed outputs of pooled layers on every block shape: 256 rows x 128 and x 64
 # channels and the split-K shape, ragged channels, 255 windows an image
 @pytest.mark.parametrize("bits", [1, 2, 3])
-@pytest.mark.parametrize("n, cout, cfg", [(130, 100, 0), (130, 48, 1), (3, 100, 2)])
+@pytest.mark.parametrize("n, cout, cfg", [(130, 100, 0), (130, 48, 1), (11, 100, 2)])
 def test_pooled_packed_output(dev, n, cout, cfg, bits):
     cin, h, w = 40, 30, 34
     g = synth.generator(34)
@@ -112,3 +112,73 @@ def test_pooled_packed_output(dev, n, cout, cfg, bits):
     np.testing.assert_array_equal(unpack_act(got.cpu().numpy(), n, cout, h // 2, w // 2, bits),
                                   oracle.quantize(oracle.hardtanh(z), bits))
     assert tail_bits_zero(got.cpu().numpy(), cout, bits)
+
+
+# layers of few output tiles: each block shape of the kernel for them (one
+# channel tile and 4 or 8 waves, two and 8), its last tile partly or wholly past
+# the last pixel or channel, every epilogue, pooled and not, strides, 1 x 1 and
+# a kernel that covers the map, and both sides of its 1024-tile limit
+LAT_CASES = [
+    # n, cin, h, w, cout, k, stride, pad, shape (channel tiles, waves; None: another kernel)
+    (1, 64, 56, 56, 64, 3, 1, 1, (1, 4)),
+    (3, 70, 9, 7, 40, 3, 1, 1, (1, 4)),
+    (2, 33, 11, 13, 31, 3, 2, 1, (1, 4)),
+    (1, 512, 7, 7, 200, 3, 1, 1, (1, 8)),
+    (5, 512, 4, 4, 70, 4, 1, 0, (1, 8)),
+    (12, 260, 14, 14, 150, 3, 1, 1, (2, 8)),
+    (7, 128, 28, 28, 128, 1, 2, 0, (1, 4)),
+    (32, 96, 32, 32, 32, 1, 1, 0, (1, 4)),
+    (33, 96, 32, 32, 32, 3, 1, 1, None),
+]
+
+
+@pytest.mark.parametrize("ab, wb", [(1, 1), (2, 1), (1, 2), (2, 2), (3, 3), (3, 1)])
+@pytest.mark.parametrize("case", LAT_CASES)
+def test_few_output_tiles(dev, case, ab, wb):
+    n, cin, h, w, cout, k, s, p, shape = case
+    g = synth.generator(35 + n + cin)
+    x = _x(36 + n, (n, cin, h, w))
+    wt = synth.normal(g, (cout, cin, k, k), 2.0 / (k * k * cin))
+    kk, bb = synth.uniform(g, (cout,), 0.001, 0.05), synth.normal(g, (cout,), 0.1)
+    ho, wo = q.out_size(h, k, s, p), q.out_size(w, k, s, p)
+    act = q.pack_act(x.to(dev), ab)
+    wq, sc = q.pack_weight(wt.to(dev), wb)
+    lw, osc = oracle.quantize_weights(wt.numpy(), wb)
+    acc = oracle.qconv_acc(oracle.quantize(x.numpy(), ab), lw, ab, s, p)
+    shift = oracle.level_shift(ab) + oracle.level_shift(wb)
+    algo = q.ALGO_MFMA_FP4
+    for pool in (False, True):
+        if pool and (ho < 2 or wo < 2):
+            continue
+        flags = q.EPI_POOL2 if pool else 0
+        name = q.kernel_name(n, cin, h, w, cout, k, s, p, ab, wb, flags=flags, algo=algo)
+        if not pool:
+            want = f"conv_mfma_lat_kernel<{q.planes(ab)}, {shape[0]}, {shape[1]}, 0>" if shape else "conv_mfma_kernel"
+            assert name.startswith(want), name
+        a = acc
+        if pool:
+            oh, ow = ho // 2, wo // 2
+            a = acc[:, :, :2 * oh, :2 * ow].reshape(n, cout, oh, 2, ow, 2).max(axis=(3, 5))
+        z = oracle.epi_bn(a, kk.numpy(), bb.numpy(), shift)
+        res = synth.normal(g, z.shape, 1.0)
+        args = (act, wq, n, cin, h, w, cout, k, s, p, ab, wb)
+        kw = dict(bn_k=kk.to(dev), bn_b=bb.to(dev), algo=algo)
+        out, _ = q.conv(*args, flags=flags, algo=algo)
+        np.testing.assert_array_equal(out.cpu().numpy(), a)
+        out, _ = q.conv(*args, mode=q.EPI_SCALE_F32, flags=flags, scale=sc, algo=algo)
+        np.testing.assert_array_equal(out.cpu().numpy(), oracle.epi_scale(a, osc, shift))
+        for ob in (1, 2, 3):
+            words = q.packed_act_words(n, cout, z.shape[2], z.shape[3], ob)
+            outp = torch.full((words + 16,), 0x5A5A5A5A, dtype=torch.int32, device=dev)
+            q.conv(*args, mode=q.EPI_BN_PACK, flags=flags, out_bits=ob, out_packed=outp[:words], **kw)
+            got = outp.cpu().numpy()
+            np.testing.assert_array_equal(unpack_act(got[:words], n, cout, *z.shape[2:], ob),
+                                          oracle.quantize(oracle.hardtanh(z), ob))
+            assert tail_bits_zero(got[:words], cout, ob) and (got[words:] == 0x5A5A5A5A).all()
+        outp = torch.empty(words, dtype=torch.int32, device=dev)
+        zr = oracle.add(z, res.numpy())
+        out, _ = q.conv(*args, mode=q.EPI_BN_F32, flags=flags | q.EPI_RESIDUAL, residual=res.to(dev), out_bits=3,
+                        out_packed=outp, **kw)
+        np.testing.assert_array_equal(out.cpu().numpy(), zr)
+        np.testing.assert_array_equal(unpack_act(outp.cpu().numpy(), n, cout, *z.shape[2:], 3),
+                                      oracle.quantize(oracle.hardtanh(zr), 3))
