@@ -182,3 +182,31 @@ def test_few_output_tiles(dev, case, ab, wb):
         np.testing.assert_array_equal(out.cpu().numpy(), zr)
         np.testing.assert_array_equal(unpack_act(outp.cpu().numpy(), n, cout, *z.shape[2:], 3),
                                       oracle.quantize(oracle.hardtanh(zr), 3))
+
+
+# fp16 operands: the weight ring of 3 x 3 layers on both 256-row shapes, with one
+# and two words per stage (whole small images, runs of one image), a last stage
+# of one word, and the layers beside it (another kernel size)
+@pytest.mark.parametrize("ab, wb", [(1, 16), (2, 16), (3, 16), (16, 1)])
+@pytest.mark.parametrize("n, cin, h, cout, k", [(256, 160, 7, 320, 3), (70, 96, 28, 128, 3), (70, 32, 28, 64, 3),
+                                                (40, 64, 28, 128, 5)])
+def test_fp16_integer_values(dev, n, cin, h, cout, k, ab, wb):
+    g = synth.generator(37 + cin)
+    small = torch.randint(-3, 4, (n, cin, h, h), generator=g).float()  # integers: every partial sum is exact in fp32
+    x = small if ab == 16 else _x(38, (n, cin, h, h))
+    wt = torch.randint(-3, 4, (cout, cin, k, k), generator=g).float() if wb == 16 else \
+        synth.normal(g, (cout, cin, k, k), 2.0 / (k * k * cin))
+    kk, bb = synth.uniform(g, (cout,), 0.001, 0.05), synth.normal(g, (cout,), 0.1)
+    wq, _ = q.pack_weight(wt.to(dev), wb)
+    out, _ = q.conv(q.pack_act(x.to(dev), ab), wq, n, cin, h, h, cout, k, 1, k // 2, ab, wb, mode=q.EPI_BN_F32,
+                    bn_k=kk.to(dev), bn_b=bb.to(dev))
+    m = min(n, 6)  # the first and the last images against the oracle
+    idx = list(range(m // 2)) + list(range(n - m // 2, n))
+    if wb == 16:
+        want = oracle.qconv16w_layer(oracle.quantize(x[idx].numpy(), ab), oracle.to_f16(wt.numpy()), ab, 1, k // 2, "bn",
+                                     k=kk.numpy(), b=bb.numpy())
+    else:
+        lw, _ = oracle.quantize_weights(wt.numpy(), wb)
+        want = oracle.qconv16_layer(oracle.to_f16(x[idx].numpy()), lw, wb, 1, k // 2, "bn", k=kk.numpy(), b=bb.numpy())
+    want = want[0] if isinstance(want, tuple) else want
+    np.testing.assert_array_equal(out.cpu().numpy()[idx], want)
