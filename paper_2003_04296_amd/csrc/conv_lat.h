@@ -33,27 +33,6 @@
 namespace qc {
 namespace mfma {
 
-// Bits t of [0, k) whose position p + t lies in [0, n).
-__device__ __forceinline__ uint32_t tap_mask(int p, int n, int k) {
-  const int lo = min(max(-p, 0), k), hi = min(max(n - p, 0), k);
-  return ((1u << hi) - 1u) & ~((1u << lo) - 1u);
-}
-
-template <int PA>
-__device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rsrc, int voff, int soff, uint32_t* w) {
-  if constexpr (PA == 1) {
-    w[0] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, soff, 0);
-  } else if constexpr (PA == 2) {
-    const auto v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, soff, 0);
-    w[0] = v[0];
-    w[1] = v[1];
-  } else {
-    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, soff, 0);
-#pragma unroll
-    for (int p = 0; p < 4; ++p) w[p] = v[p];
-  }
-}
-
 // k-steps whose reads are in flight together (6 the same, 9 slower: the code
 // of the steps past a wave's range costs more than a second round saves)
 constexpr int LAT_D = 5;

@@ -161,6 +161,7 @@ struct MfmaArgs {
   int out_bytes;      // byte size of the unpacked output (buffer-resource bound, < 2^31)
   int buf_bytes;      // LDS bytes of one halo buffer
   int grid;           // blocks launched (each loops over the work items)
+  int direct;         // the unstaged form (direct_body): units run over all images, 256 per block
   int act_bytes;      // byte size of the packed activations (buffer-resource bound; 0 if >= 2^31)
 };
 
@@ -478,7 +479,7 @@ __device__ __forceinline__ void swap_res_load(const MfmaArgs& m, int img0, int u
 // one exchange with lane l ^ 32 completes the word, which lanes 0-31 store
 // (PERM: through v_permlane32_swap, else a shuffle through LDS, which takes
 // no extra register).
-template <int KIND, int RES = 2, int OB = 0, bool PERM = false, class AccT>
+template <int KIND, int RES = 2, int OB = 0, bool PERM = false, bool STRAIGHT = PERM, class AccT>
 __device__ __forceinline__ void tile_epilogue_swap(const MfmaArgs& m, const AccT& acc, int img0, int u0,
                                                    int T, int co32, int co_blk, const float* prm,
                                                    int lane, const float (*pre)[16] = nullptr) {
@@ -555,9 +556,9 @@ __device__ __forceinline__ void tile_epilogue_swap(const MfmaArgs& m, const AccT
         });
       }
     };
-    // PERM false (the store-overlapped kernel, which has no registers for two
-    // forms of z): one form with a branch per store
-    if ((PERM || KIND == K_INT32) && full) store_all(std::true_type{});  // uniform
+    // not STRAIGHT (the staged store-overlapped kernel, which has no registers
+    // for two forms of z): one form with a branch per store
+    if (STRAIGHT && full) store_all(std::true_type{});  // uniform
     else store_all(std::false_type{});
   }
   if constexpr (OB > 0) {
@@ -760,7 +761,7 @@ template <int KIND, int RES, int OB, int MT, int NT, class AccT>
 __device__ __forceinline__ void epilogue_swap_tiles(const MfmaArgs& m, const AccT (&acc)[MT][NT], int img0,
                                                     int u0, int tile_m0, int co_w, int co_blk, const float* prm,
                                                     int lane) {
-  Unroll<0, MT * NT>::run([&](auto TT) {
+  Unroll<0, MT * NT>::run([&](auto TT) __attribute__((always_inline)) {
     constexpr int tt = decltype(TT)::value;
     const int co32 = co_w + 32 * (tt % NT);
     if (co32 < m.c.cout)  // uniform
@@ -972,6 +973,151 @@ __device__ __forceinline__ void load_params(const ConvArgs& a, int co_blk, int t
     else if (a.mode == QCONV_EPI_BN_F32 || a.mode == QCONV_EPI_BN_PACK) v = half ? a.bn_b[cs] : a.bn_k[cs];
     prm[half * 128 + c] = v;
   }
+}
+
+// Bits t of [0, k) whose position p + t lies in [0, n).
+__device__ __forceinline__ uint32_t tap_mask(int p, int n, int k) {
+  const int lo = min(max(-p, 0), k), hi = min(max(n - p, 0), k);
+  return ((1u << hi) - 1u) & ~((1u << lo) - 1u);
+}
+
+template <int PA>
+__device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rsrc, int voff, int soff, uint32_t* w) {
+  if constexpr (PA == 1) {
+    w[0] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, soff, 0);
+  } else if constexpr (PA == 2) {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, soff, 0);
+    w[0] = v[0];
+    w[1] = v[1];
+  } else {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, soff, 0);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) w[p] = v[p];
+  }
+}
+
+// The unstaged form of the store-overlapped kernel's 64-channel shape (fp4,
+// 1- and 2-bit inputs): no tiles in LDS and no barrier, blocks of four
+// independent waves in place of two groups that take turns.  A wave owns 64
+// pixels (of all images, in order) x 64 channels; a lane reads the packed word
+// of its own pixels for each (tap, k-step), D steps ahead, expands it into its
+// operand fragment in registers and meets the weight fragments read the same
+// way, and one wave's epilogue and stores run under another's products.  Where
+// a layer has few k-steps, the staged forms spend more on a block's weights,
+// halo tiles and barriers, and on the part of a 256-pixel item past the end of
+// an image, than these repeated expansions cost.  Measured at 2 bits (before:
+// the staged form): ResNet-18 batch 64, 64 x 56 x 56 with residual and packed
+// copy 31.6 -> 25.6 us, 128 x 28 x 28 the same 23.5 -> 18.6, 64 -> 128 / 2
+// packed 14.0 -> 9.0.  D = 2 and four waves a SIMD: with 3 or 4 steps ahead
+// and three waves the 64-channel layers measured 5-10 % slower, the deeper
+// ones 2-5 % faster; 3-bit inputs spill within 128 registers.
+template <int PA, int D, class Epi>
+__device__ __forceinline__ void direct_body(const MfmaArgs& m, Epi&& epi) {
+  constexpr int MT = 2, NT = 2, WM = 4, BCO = 32 * NT;
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
+  const ConvArgs& a = m.c;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 5, r32 = lane & 31;
+  float* prm = reinterpret_cast<float*>(lds_raw);
+  const int pt = (int)blockIdx.x / m.tiles_co;
+  const int co_blk = ((int)blockIdx.x - pt * m.tiles_co) * BCO;
+  const int T0 = (pt * WM + wave) * MT;
+  // this thread's epilogue parameters, stored to LDS after the products (read
+  // through buffer resources that are empty for a mode without them, so that
+  // no branch makes the compiler wait for them here)
+  const bool bn = a.mode == QCONV_EPI_BN_F32 || a.mode == QCONV_EPI_BN_PACK;
+  const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(bn ? a.bn_k : a.scale), (short)0, a.mode == QCONV_EPI_INT32 ? 0 : a.cout * 4, 0x00020000);
+  const __amdgpu_buffer_rsrc_t prsrc =
+      __builtin_amdgcn_make_buffer_rsrc((void*)a.bn_b, (short)0, bn ? a.cout * 4 : 0, 0x00020000);
+  const int pvoff = tid < BCO ? (co_blk + tid) * 4 : 0x7FFFFFF0;
+  const uint32_t pk = __builtin_amdgcn_raw_buffer_load_b32(krsrc, pvoff, 0, 0);
+  const uint32_t pb = __builtin_amdgcn_raw_buffer_load_b32(prsrc, pvoff, 0, 0);
+  // byte offset of each row's first tap word (this lane's k-half; may lie
+  // before the tensor) and the taps inside the image
+  const int apix = a.cw * PA * 4;
+  const int total = a.n * m.upi;
+  int base[MT];
+  uint32_t rmask[MT], cmask[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    const int unit = 32 * (T0 + i) + r32;
+    const int img = (int)fdiv((uint32_t)unit, m.fd_upi);
+    const int uu = unit - img * m.upi;
+    const int uy = (int)fdiv((uint32_t)uu, m.fd_uw);
+    const int iy = uy * a.stride - a.pad, ix = (uu - uy * m.uw) * a.stride - a.pad;
+    base[i] = ((img * a.h + iy) * a.w + ix) * apix + g * (PA * 4);
+    rmask[i] = unit < total ? tap_mask(iy, a.h, a.kh) : 0u;
+    cmask[i] = tap_mask(ix, a.w, a.kw);
+  }
+  const __amdgpu_buffer_rsrc_t arsrc =
+      __builtin_amdgcn_make_buffer_rsrc((void*)a.act, (short)0, m.act_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t brsrc =
+      __builtin_amdgcn_make_buffer_rsrc((void*)m.wx, (short)0, m.wx_bytes, 0x00020000);
+  const int bvoff = (co_blk + r32) * 32 + g * 16;
+  const int bstride = a.cop * 32;
+  const int nsteps = a.kh * a.kw * m.ksteps;
+  int step = 0, ks = 0, ky = 0, kx = 0;
+  int voff[MT];
+  auto tap_offsets = [&]() __attribute__((always_inline)) {
+    const int to = (ky * a.w + kx) * apix;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      voff[i] = ((rmask[i] >> ky) & (cmask[i] >> kx) & 1u) ? base[i] + to : 0x7FFFFFF0;
+  };
+  tap_offsets();
+  uint32_t ra[D][MT][PA];
+  v4i rb[D][NT];
+  // reads of the next step; past the last one beyond both buffers (0, no access)
+  auto issue = [&](auto DD) __attribute__((always_inline)) {
+    constexpr int d = decltype(DD)::value;
+    const bool in = step < nsteps;
+    const int ao = in ? ks * (2 * PA * 4) : 0x7FFF0000, bo = in ? step * bstride : m.wx_bytes;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) load_words<PA>(arsrc, voff[i], ao, ra[d][i]);
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+      rb[d][j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(brsrc, bvoff + j * 1024, bo, 0));
+    ++step;
+    if (++ks == m.ksteps) {  // uniform
+      ks = 0;
+      if (++kx == a.kw) {
+        kx = 0;
+        ++ky;
+      }
+      tap_offsets();
+    }
+  };
+  v16f acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+  Unroll<0, D>::run([&](auto dd) { issue(dd); });
+  for (int s0 = 0; s0 < nsteps; s0 += D) {
+    Unroll<0, D>::run([&](auto dd) __attribute__((always_inline)) {
+      constexpr int d = decltype(dd)::value;
+      if (s0 + d < nsteps) {  // uniform
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          uint32_t o[4];
+          expand_fp4_word<PA>(ra[d][i], 0xFFFFFFFFu, o);
+          const v4i A = {(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
+#pragma unroll
+          for (int j = 0; j < NT; ++j) acc[i][j] = mfma<OP_FP4>(rb[d][j], A, acc[i][j]);
+        }
+      }
+      issue(dd);
+    });
+  }
+  if (tid < BCO) {
+    prm[tid] = __uint_as_float(pk);
+    prm[128 + tid] = __uint_as_float(pb);
+  }
+  lds_barrier();
+  epi(acc, T0, co_blk, prm, lane);
 }
 
 // The convolution kernel.  Blocks loop over work items (pixel tile x channel
@@ -1414,6 +1560,30 @@ __global__ __launch_bounds__(1024, 1) void conv_mfma_pp_kernel(const MfmaArgs m)
   constexpr int NI = PA == 4 ? 2 : 3;  // halo items per thread held in registers
   extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
   const ConvArgs& a = m.c;
+  if constexpr (OPK == OP_FP4 && CFG == 1 && PA <= 2) {
+    if (m.direct) {  // uniform over the launch (blocks of 256 threads)
+      direct_body<PA, 2>(m, [&](const v16f (&acc)[2][2], int T0, int co, const float* prm, int lane)
+                                __attribute__((always_inline)) {
+        Unroll<0, 4>::run([&](auto TT) __attribute__((always_inline)) {
+          constexpr int t = decltype(TT)::value;
+          const int co32 = co + 32 * (t % 2);
+          if (co32 >= a.cout) return;  // uniform
+          const v16f& A = acc[t / 2][t % 2];
+          const int T = T0 + t / 2;
+          if (a.mode == QCONV_EPI_INT32) {
+            tile_epilogue_swap<K_INT32, 0, 0, true>(m, A, 0, 0, T, co32, co, prm, lane);
+          } else if (a.mode == QCONV_EPI_SCALE_F32) {
+            tile_epilogue_swap<K_SCALE, 0, 0, true>(m, A, 0, 0, T, co32, co, prm, lane);
+          } else if (a.mode == QCONV_EPI_BN_PACK) {
+            if constexpr (OB > 0) tile_epilogue_swap<K_PACK, 0, OB, true>(m, A, 0, 0, T, co32, co, prm, lane);
+          } else {
+            tile_epilogue_swap<K_BNF32, 2, OB, true>(m, A, 0, 0, T, co32, co, prm, lane);
+          }
+        });
+      });
+      return;
+    }
+  }
   // wave-uniform indices in scalar registers
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave >> 3, wq = wave & 7;
@@ -1615,7 +1785,10 @@ __global__ __launch_bounds__(1024, 1) void conv_mfma_pp_kernel(const MfmaArgs m)
         if (st && co32 < a.cout) {
           const int T = wm * MT + i;
           if (a.mode == QCONV_EPI_INT32) {
-            tile_epilogue_swap<K_INT32, 0>(m, acc[i][j], pimg0, pu0, T, co32, co_blk, prm, plane);
+            // straight stores where the 64-channel shape has the registers
+            // (3W3A 256 x 64 x 56 x 56 53.6 -> 50.5 us; the 128-channel one spilled:
+            // 21.6 -> 24.7 us)
+            tile_epilogue_swap<K_INT32, 0, 0, false, CFG == 1>(m, acc[i][j], pimg0, pu0, T, co32, co_blk, prm, plane);
           } else if (a.mode == QCONV_EPI_SCALE_F32) {
             tile_epilogue_swap<K_SCALE, 0>(m, acc[i][j], pimg0, pu0, T, co32, co_blk, prm, plane);
           } else if (a.mode == QCONV_EPI_BN_PACK) {
@@ -1675,6 +1848,7 @@ int launch_conv_lat(const ConvArgs& a, hipStream_t s);
 int device_cus();
 bool use_swap(const MfmaArgs& m);
 bool use_pp(const MfmaArgs& m, int cfg, int cus);
+bool direct_applies(const ConvArgs& a, MfmaArgs* m);
 size_t pp_lds(const MfmaArgs& m, int cfg);
 size_t block_lds(const MfmaArgs& m);
 constexpr int LDS_PER_CU = 160 * 1024;
@@ -1698,6 +1872,17 @@ bool raise_lds_limit_of(size_t bytes) {
 
 template <int OPK, int PA, int CFG>
 int launch_cfg(MfmaArgs m, hipStream_t s) {
+  if constexpr (OPK == OP_FP4 && CFG == 1 && PA <= 2) {
+    MfmaArgs dm;
+    if (direct_applies(m.c, &dm)) {
+      const dim3 grid((unsigned)(dm.tiles_px * dm.tiles_co));
+      if (m.c.out_packed)  // PA planes: the input's width, as direct_applies asks
+        conv_mfma_pp_kernel<OPK, PA, CFG, PA><<<grid, 256, PARAM_BYTES, s>>>(dm);
+      else
+        conv_mfma_pp_kernel<OPK, PA, CFG, 0><<<grid, 256, PARAM_BYTES, s>>>(dm);
+      return hip_status();
+    }
+  }
   const size_t lds = block_lds(m);
   const int total = m.tiles_px * m.tiles_co;
   const int cus = device_cus();

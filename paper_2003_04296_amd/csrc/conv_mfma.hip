@@ -173,14 +173,61 @@ int pick_cfg_base(const ConvArgs& a) {
   return big;
 }
 
+// Whether a layer takes the unstaged form of the store-overlapped kernel
+// (direct_body), and its arguments.  Up to 9 k-steps (3 x 3 over 64 channels)
+// it is the faster one at every map size measured; up to 18 where 256-pixel
+// items leave part of an item past an image's end (28 x 28 batch 256: 38.9 ->
+// 33.1 us; 32 x 32, full items, batch 128: 22.7 us staged, 23.5 unstaged), but
+// not for a packed output alone, which the base kernel runs; past that the
+// staged forms win (256 x 14 x 14 batch 128, 36 steps: 20.3 us staged, 20.7).
+// Over 4096 tiles of 32 x 32 (16 a CU); with fewer the smaller shapes serve.
+bool direct_applies(const ConvArgs& a, MfmaArgs* m) {
+  if (a.mfma_op != OP_FP4 || a.a_bits > 2 || a.pool || a.stride > 2 || a.kh > 16 || a.kw > 16 || a.n < 1) return false;
+  if (a.out_packed && ((a.mode != QCONV_EPI_BN_F32 && a.mode != QCONV_EPI_BN_PACK) || a.out_bits != a.a_bits))
+    return false;
+  const int64_t upi = (int64_t)a.ho * a.wo, units = a.n * upi;
+  const int64_t tiles = (units + 31) / 32 * ceil_div(a.cout, 32);
+  const int ksteps = ceil_div(a.cw, 2), steps = a.kh * a.kw * ksteps;
+  const bool full = upi % 256 == 0 || (upi < 256 && 256 % upi == 0);
+  if (tiles <= 4096 || a.cout > 256) return false;
+  if (steps > 9 && (steps > 18 || full || a.mode == QCONV_EPI_BN_PACK)) return false;
+  const int64_t wxb = (int64_t)a.kh * a.kw * ksteps * a.cop * 32;
+  const int64_t ab = (int64_t)a.n * a.h * a.w * a.cw * act_words(a.a_bits) * 4;
+  const int64_t ob = units * a.cout * 4;
+  // buffer offsets past the end stay below 2^31; exact fast divisions
+  if (wxb >= ((int64_t)1 << 30) || ab >= ((int64_t)1 << 30) || ob >= ((int64_t)1 << 31) ||
+      (units + 256) * upi >= ((int64_t)1 << 32) || upi * a.wo >= ((int64_t)1 << 32))
+    return false;
+  memset(m, 0, sizeof(*m));
+  m->c = a;
+  m->direct = 1;
+  m->ksteps = ksteps;
+  m->wx = a.w_fp4;
+  m->wx_bytes = (int)wxb;
+  m->act_bytes = (int)ab;
+  m->out_bytes = (int)ob;
+  m->uw = a.wo;
+  m->upi = (int)upi;
+  m->units_pb = 256;
+  m->ipb = a.n + (a.n == 1);  // units run over all images (more than one: image = unit / upi)
+  m->fd_upi = make_fastdiv((uint32_t)m->upi);
+  m->fd_uw = make_fastdiv((uint32_t)m->uw);
+  m->tiles_px = (int)((units + 255) / 256);
+  m->tiles_co = ceil_div(a.cout, 64);
+  m->inv = 1.0f / (float)(1 << a.shift);
+  m->othr = thr_unclamped(a.othr);
+  return true;
+}
+
 // The store-overlapped kernel needs two items per CU: a layer whose
 // 128-channel items are too few for it takes 64-channel items when those
 // are enough (its epilogue then runs beside the other group's MFMAs instead
 // of after them).
 int pick_cfg(const ConvArgs& a) {
+  MfmaArgs m0, m1;
+  if (direct_applies(a, &m0) && plan(a, 1, &m1)) return 1;  // (the shape of its name)
   const int cfg = pick_cfg_base(a);
   if (cfg != 0) return cfg;
-  MfmaArgs m0, m1;
   const int cus = device_cus();
   if (plan(a, 0, &m0) && !use_pp(m0, 0, cus) && plan(a, 1, &m1) && use_pp(m1, 1, cus)) return 1;
   return 0;
@@ -257,9 +304,10 @@ int mfma_kernel_name(const ConvArgs& a, char* buf, int len) {
   const int cfg = pick_cfg(a);
   if (!plan(a, cfg, &m)) return QCONV_EUNSUPPORTED;
   char name[96];
+  MfmaArgs d;
   if (lat_applies(a))
     lat_kernel_name(a, name, (int)sizeof(name));
-  else if (use_pp(m, cfg, device_cus()))
+  else if (direct_applies(a, &d) || use_pp(m, cfg, device_cus()))
     snprintf(name, sizeof(name), "conv_mfma_pp_kernel<%d, %d, %d, %d>", a.mfma_op, act_words(a.a_bits), cfg,
              a.out_packed ? a.out_bits : 0);
   else

@@ -210,3 +210,61 @@ def test_fp16_integer_values(dev, n, cin, h, cout, k, ab, wb):
         want = oracle.qconv16_layer(oracle.to_f16(x[idx].numpy()), lw, wb, 1, k // 2, "bn", k=kk.numpy(), b=bb.numpy())
     want = want[0] if isinstance(want, tuple) else want
     np.testing.assert_array_equal(out.cpu().numpy()[idx], want)
+
+
+# the unstaged form of the store-overlapped kernel (its 64-channel shape on 1- and
+# 2-bit inputs): ragged maps, channels and batches (a last block of a few
+# pixels, waves and channel tiles with nothing to do), strides, 1 x 1, one and
+# two k-steps a tap, and the layers beside its limits, on the staged kernels
+DIRECT_CASES = [
+    # n, cin, h, w, cout, k, stride, pad, packed output alone on it too
+    (37, 40, 56, 57, 100, 3, 1, 1, True),
+    (67, 64, 55, 56, 130, 1, 2, 0, True),
+    (3, 64, 150, 151, 64, 3, 1, 1, True),
+    (70, 100, 28, 27, 90, 3, 1, 1, False),
+    (46, 64, 33, 29, 96, 3, 1, 1, True),
+]
+
+
+@pytest.mark.parametrize("ab, wb", [(1, 1), (2, 1), (2, 2), (1, 3)])
+@pytest.mark.parametrize("case", DIRECT_CASES)
+def test_unstaged_form(dev, case, ab, wb):
+    n, cin, h, w, cout, k, s, p, packs = case
+    g = synth.generator(39 + n + cin)
+    x = _x(40 + n, (n, cin, h, w))
+    wt = synth.normal(g, (cout, cin, k, k), 2.0 / (k * k * cin))
+    kk, bb = synth.uniform(g, (cout,), 0.001, 0.05), synth.normal(g, (cout,), 0.1)
+    ho, wo = q.out_size(h, k, s, p), q.out_size(w, k, s, p)
+    res = synth.normal(g, (n, cout, ho, wo), 1.0)
+    act = q.pack_act(x.to(dev), ab)
+    wq, sc = q.pack_weight(wt.to(dev), wb)
+    lw, osc = oracle.quantize_weights(wt.numpy(), wb)
+    acc = oracle.qconv_acc(oracle.quantize(x.numpy(), ab), lw, ab, s, p)
+    shift = oracle.level_shift(ab) + oracle.level_shift(wb)
+    z = oracle.epi_bn(acc, kk.numpy(), bb.numpy(), shift)
+    geo = (n, cin, h, w, cout, k, s, p, ab, wb)
+    algo = q.ALGO_MFMA_FP4
+    assert q.kernel_name(*geo, algo=algo) == f"conv_mfma_pp_kernel<1, {ab}, 1, 0>"
+    name = q.kernel_name(*geo, mode=q.EPI_BN_PACK, out_bits=ab, packed_out=True, algo=algo)
+    assert (name == f"conv_mfma_pp_kernel<1, {ab}, 1, {ab}>") == packs, name
+    out, _ = q.conv(act, wq, *geo, algo=algo)
+    np.testing.assert_array_equal(out.cpu().numpy(), acc)
+    out, _ = q.conv(act, wq, *geo, mode=q.EPI_SCALE_F32, scale=sc, algo=algo)
+    np.testing.assert_array_equal(out.cpu().numpy(), oracle.epi_scale(acc, osc, shift))
+    kw = dict(bn_k=kk.to(dev), bn_b=bb.to(dev), algo=algo)
+    out, _ = q.conv(act, wq, *geo, mode=q.EPI_BN_F32, **kw)
+    np.testing.assert_array_equal(out.cpu().numpy(), z)
+    for ob in (ab, 3):  # the input's width, and one that another kernel serves
+        words = q.packed_act_words(n, cout, ho, wo, ob)
+        outp = torch.full((words + 16,), 0x5A5A5A5A, dtype=torch.int32, device=dev)
+        q.conv(act, wq, *geo, mode=q.EPI_BN_PACK, out_bits=ob, out_packed=outp[:words], **kw)
+        got = outp.cpu().numpy()
+        np.testing.assert_array_equal(unpack_act(got[:words], n, cout, ho, wo, ob),
+                                      oracle.quantize(oracle.hardtanh(z), ob))
+        assert tail_bits_zero(got[:words], cout, ob) and (got[words:] == 0x5A5A5A5A).all()
+        zr = oracle.add(z, res.numpy())
+        out, _ = q.conv(act, wq, *geo, mode=q.EPI_BN_F32, flags=q.EPI_RESIDUAL, residual=res.to(dev), out_bits=ob,
+                        out_packed=outp[:words], **kw)
+        np.testing.assert_array_equal(out.cpu().numpy(), zr)
+        np.testing.assert_array_equal(unpack_act(outp.cpu().numpy()[:words], n, cout, ho, wo, ob),
+                                      oracle.quantize(oracle.hardtanh(zr), ob))
