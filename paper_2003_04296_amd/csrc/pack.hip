@@ -140,7 +140,7 @@ __global__ __launch_bounds__(1024) void pack_act_lds_kernel(const float* __restr
 
 // The same for maps of a few pixels (fully connected inputs): lanes along the
 // channels, a plane's two words of a 64-channel unit are one wave ballot.  A
-// wave takes U units.  (A unit count past 2^32 would need over 500 GB of x.)
+// wave takes U units.
 template <int BITS>
 __global__ __launch_bounds__(256) void pack_act_chan_kernel(const float* __restrict__ x, int c, int hw, int cwn,
                                                             uint32_t units, Thr t, uint32_t* __restrict__ out) {
@@ -616,14 +616,27 @@ int launch_pack_act(const float* x, int n, int c, int h, int w, int bits, Thr t,
 #undef QC_PACK
     return hip_status();
   }
-  const uint32_t units = (uint32_t)(npix * ceil_div(cwn, 2));
-  const dim3 grid((units + 15) / 16);
-  switch (bits) {
-    case 1: pack_act_chan_kernel<1><<<grid, 256, 0, s>>>(x, c, hw, cwn, units, t, out); break;
-    case 2: pack_act_chan_kernel<2><<<grid, 256, 0, s>>>(x, c, hw, cwn, units, t, out); break;
-    default: pack_act_chan_kernel<3><<<grid, 256, 0, s>>>(x, c, hw, cwn, units, t, out); break;
+  // images in runs whose grids stay below 2^31 threads (16 per unit; a launch
+  // takes fewer than 2^32) and whose unit indices fit 32 bits: one launch
+  // below 2^27 units
+  const int64_t upi = (int64_t)hw * ceil_div(cwn, 2), limit = (int64_t)1 << 27;
+  const int per = (int)(upi < limit ? (limit / upi < n ? limit / upi : n) : 1);
+  for (int i = 0; i < n;) {
+    const int m = n - i < per ? n - i : per;
+    const uint32_t units = (uint32_t)(m * upi);
+    const dim3 grid((unsigned)(((int64_t)units + 15) / 16));
+    const float* xi = x + (int64_t)i * c * hw;
+    uint32_t* oi = out + (int64_t)i * hw * cwn * planes_of(bits);
+    switch (bits) {
+      case 1: pack_act_chan_kernel<1><<<grid, 256, 0, s>>>(xi, c, hw, cwn, units, t, oi); break;
+      case 2: pack_act_chan_kernel<2><<<grid, 256, 0, s>>>(xi, c, hw, cwn, units, t, oi); break;
+      default: pack_act_chan_kernel<3><<<grid, 256, 0, s>>>(xi, c, hw, cwn, units, t, oi); break;
+    }
+    const int rc = hip_status();
+    if (rc) return rc;
+    i += m;
   }
-  return hip_status();
+  return QCONV_OK;
 }
 
 int launch_pack_act_f16(const float* x, int n, int c, int h, int w, uint32_t* out, hipStream_t s) {

@@ -52,6 +52,16 @@ def test_pack_act(dev, bits, shape):
         assert (got[:off] == 0x5A5A5A5A).all() and (got[off + words:] == 0x5A5A5A5A).all()
 
 
+# past 2^27 units of the lanes-along-the-channels kernel: several launches
+def test_pack_act_many_images(dev):
+    n = (1 << 27) + 5
+    x = torch.empty((n, 1, 1, 1), dtype=torch.float32, device=dev).uniform_(-1, 1)
+    out = torch.full((n + 8,), 0x5A5A5A5A, dtype=torch.int32, device=dev)
+    q.pack_act(x, 1, out=out[:n])
+    assert torch.equal(out[:n], (x.view(-1) > 0).int())
+    assert (out[n:] == 0x5A5A5A5A).all()
+
+
 # through LDS from 65536 (pixel, word) pairs on (here 2 and 9 words per
 # pixel), directly below
 @pytest.mark.parametrize("shape", [(33, 40, 32, 32), (8, 270, 31, 31), (3, 40, 9, 9)])
