@@ -230,7 +230,11 @@ __global__ __launch_bounds__(256) void avgpool_lds_kernel(const float* __restric
 // owns 4 consecutive outputs.  Per chunk of inputs the block stages, with
 // all of its loads in flight at once, the 64 images' inputs and the 4 weight
 // rows in LDS; lanes then read their own input row (16-byte reads, padded
-// rows) and the wave's weight row as a broadcast.
+// rows) and the wave's weight row as a broadcast, both read one group of 16
+// links ahead of the chain.  Bound by the chain: 1024 packed inputs -> 10 at
+// batch 256 12.4 -> 9.5 us (reads at the head of each group before); 512 fp32
+// inputs -> 1000 at batch 64 10.0 -> 9.9, at batch 1 9.5 -> 9.1 us, where
+// staging the three chunks weighs more.
 //
 // x_bits = 0: x is fp32 [n][in].  x_bits = 1: x is the packed sign plane
 // [n][ceil(in/32)] of {-1,+1} inputs (a 1x1 map), and fmaf(+-1, w, acc) is
@@ -297,32 +301,74 @@ __global__ __launch_bounds__(256) void fc_f32_kernel(const void* __restrict__ xi
     const float* wr = ws + wave * CI;
     if constexpr (X_BITS == 0) {
       const float* xr = reinterpret_cast<const float*>(xs) + lane * FC_XLD;
-      const int L4 = L & ~3;
-#pragma unroll 4
-      for (int k = 0; k < L4; k += 4) {
-        const float4 xv = *reinterpret_cast<const float4*>(xr + k);
-        const float4 wv = *reinterpret_cast<const float4*>(wr + k);
-        acc = fmaf(xv.x, wv.x, acc);
-        acc = fmaf(xv.y, wv.y, acc);
-        acc = fmaf(xv.z, wv.z, acc);
-        acc = fmaf(xv.w, wv.w, acc);
+      // The operands of 16 inputs are read under the 16 links of the chain
+      // before them, in two register sets (past the last group: that group
+      // again).
+      const int L16 = L & ~15, L4 = L & ~3;
+      float4 xa[4], wa[4], xb[4], wb[4];
+      auto ahead = [&](float4* x4, float4* w4, int k) __attribute__((always_inline)) {
+        const int kc = min(k, L16 - 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          x4[i] = *reinterpret_cast<const float4*>(xr + kc + 4 * i);
+          w4[i] = *reinterpret_cast<const float4*>(wr + kc + 4 * i);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      auto link4 = [&](float4 x4, float4 w4) __attribute__((always_inline)) {
+        acc = fmaf(x4.x, w4.x, acc);
+        acc = fmaf(x4.y, w4.y, acc);
+        acc = fmaf(x4.z, w4.z, acc);
+        acc = fmaf(x4.w, w4.w, acc);
+      };
+      if (L16 > 0) ahead(xa, wa, 0);
+      for (int k = 0; k < L16; k += 32) {
+        ahead(xb, wb, k + 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) link4(xa[i], wa[i]);
+        if (k + 16 >= L16) break;
+        __builtin_amdgcn_sched_barrier(0);
+        ahead(xa, wa, k + 32);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) link4(xb[i], wb[i]);
+        __builtin_amdgcn_sched_barrier(0);
       }
+      for (int k = L16; k < L4; k += 4)
+        link4(*reinterpret_cast<const float4*>(xr + k), *reinterpret_cast<const float4*>(wr + k));
       for (int k = L4; k < L; ++k) acc = fmaf(xr[k], wr[k], acc);
     } else {
       const uint32_t* xr = xs + lane * FC_XLD_BIN;
       const int full = L >> 5;
-      for (int c = 0; c < full; ++c) {
-        const uint32_t neg = ~xr[c];  // bit set <=> input -1
+      // as above: half a word's weights, and the next word, are read under the
+      // 16 links before them
+      float4 wa[4], wb[4];
+      auto ahead = [&](float4* w4, int k) __attribute__((always_inline)) {
 #pragma unroll
-        for (int k0 = 0; k0 < 32; k0 += 4) {
-          const float4 wv = *reinterpret_cast<const float4*>(wr + 32 * c + k0);
-          const float wk[4] = {wv.x, wv.y, wv.z, wv.w};
+        for (int i = 0; i < 4; ++i) w4[i] = *reinterpret_cast<const float4*>(wr + k + 4 * i);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      auto links = [&](const float4* w4, uint32_t neg, int b0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float wk[4] = {w4[i].x, w4[i].y, w4[i].z, w4[i].w};
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            const uint32_t sgn = (neg << (31 - k0 - k)) & 0x80000000u;
+            const uint32_t sgn = (neg << (31 - b0 - 4 * i - k)) & 0x80000000u;
             acc = acc + __uint_as_float(__float_as_uint(wk[k]) ^ sgn);
           }
         }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      uint32_t word = xr[0];
+      if (full > 0) ahead(wa, 0);
+      for (int c = 0; c < full; ++c) {
+        const uint32_t neg = ~word;  // bit set <=> input -1
+        const int cn = min(c + 1, full - 1);
+        word = xr[cn];
+        ahead(wb, 32 * c + 16);
+        links(wa, neg, 0);
+        ahead(wa, 32 * cn);
+        links(wb, neg, 16);
       }
       if (L & 31) {
         const uint32_t neg = ~xr[full];

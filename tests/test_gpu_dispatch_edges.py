@@ -278,3 +278,22 @@ def test_unstaged_form(dev, case, ab, wb):
         np.testing.assert_array_equal(out.cpu().numpy(), zr)
         np.testing.assert_array_equal(unpack_act(outp.cpu().numpy()[:words], n, cout, ho, wo, ob),
                                       oracle.quantize(oracle.hardtanh(zr), ob))
+
+
+# the last FC reads operands 16 inputs (fp32) or half a word (packed signs)
+# ahead: odd and even numbers of groups, remainders, one chunk and several
+@pytest.mark.parametrize("inputs", [3, 15, 16, 17, 32, 47, 64, 95, 192, 208, 223, 1024, 1056, 1071])
+@pytest.mark.parametrize("bits", [0, 1])
+def test_last_fc(dev, bits, inputs):
+    n, out = 67, 6
+    g = synth.generator(900 + inputs)
+    x = synth.normal(g, (n, inputs, 1, 1), 1.0)
+    wt = synth.normal(g, (out, inputs), 2.0 / inputs)
+    b = synth.normal(g, (out,), 0.1)
+    net = q.Net(inputs, 1, 1)
+    net.fc_f32(net.quantize(0, 1) if bits else 0, wt.to(dev), b.to(dev))
+    ws = torch.empty(max(net.workspace_bytes(n), 1), dtype=torch.uint8, device=dev)
+    got = torch.empty((n, out), dtype=torch.float32, device=dev)
+    net.forward(x.to(dev), got, ws)
+    xin = oracle.quantize(x.numpy(), 1).astype(np.float32) if bits else x.numpy()
+    np.testing.assert_array_equal(got.cpu().numpy(), oracle.fc_f32(xin.reshape(n, -1), wt.numpy(), b.numpy()))
