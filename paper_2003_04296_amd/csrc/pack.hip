@@ -483,16 +483,17 @@ __global__ __launch_bounds__(256) void pack_weight_tile_kernel(
           uint8_t* d = codes + row * pitch;
 #pragma unroll
           for (int i = 0; i < V; ++i) {
-            // plane bits of a weight (those of quant_planes, without branches)
+            // plane bits of a weight: quant_planes in its order of compares
+            // (without branches), so that weights meet thresholds that are
+            // not finite as there: s_c is data, and a NaN or infinite weight
+            // makes NaN ones (a NaN compares false: not <= it, so beyond it)
             const float x = v[r][i];
-            uint32_t b;
-            if constexpr (BITS == 1) {
-              b = x > 0.0f ? 1u : 0u;
-            } else {
+            uint32_t b = x > 0.0f ? 1u : 0u;
+            if constexpr (BITS > 1) {
               const float ax = fabsf(x);
-              b = x > t0 ? 1u : 0u;
-              if constexpr (BITS == 2) b |= !(ax <= t0) ? 2u : 0u;
-              else b |= !(ax <= t2) ? 2u : (!(ax <= t1) ? 4u : (!(ax <= t0) ? 8u : 0u));
+              if constexpr (BITS == 2) b |= 2u;
+              else b |= ax <= t1 ? 8u : (ax <= t2 ? 4u : 2u);
+              if (ax <= t0) b = 0u;
             }
             d[off[i]] = (uint8_t)b;
           }

@@ -99,6 +99,39 @@ def test_pack_weight(dev, bits, shape):
         np.testing.assert_array_equal(weight_copy_f16(words, cout, cin, kh, kw, bits), lv)
 
 
+# channels whose scale or thresholds are not finite, or zero, in every packing kernel
+# (one pass with 16- and 4-byte loads, the gather past its taps): a NaN weight, one
+# and two infinities, zeros alone, denormals, with thresholds 0 and infinite
+# (0 x inf and inf x 0 make NaN thresholds) beside the defaults
+NONFINITE_THR = {1: [None], 2: [None, (0.0,), (float("inf"),)],
+                 3: [None, (0.0, 0.0, 0.0), (0.0, 0.25, 0.5), (0.0, 0.0, 0.5), (0.125, float("inf"), float("inf"))]}
+
+
+@pytest.mark.parametrize("bits, base", [(b, t) for b in (1, 2, 3) for t in NONFINITE_THR[b]])
+@pytest.mark.parametrize("shape", [(9, 64, 3, 3), (9, 63, 3, 3), (2056, 516, 1, 1), (10, 70, 5, 5), (10, 70, 6, 6)])
+def test_pack_weight_not_finite(dev, bits, base, shape):
+    cout, cin, kh, kw = shape
+    nan, inf = float("nan"), float("inf")
+    w = synth.normal(synth.generator(41), shape, 2.0 / (cin * kh * kw))
+    flat = w.view(cout, -1)
+    flat[0, 1] = nan
+    flat[1, 2] = inf
+    flat[2, 3:5] = torch.tensor([inf, -inf])
+    flat[3] = 0.0
+    flat[3, ::2] = -0.0
+    flat[4, 5:7] = torch.tensor([nan, -inf])
+    flat[5] *= 1e-38
+    flat[cout - 1, -1] = nan  # beside an all-finite channel of the same block
+    lv, s = oracle.quantize_weights(w.numpy(), bits, base_thr=base)
+    words, scale = q.pack_weight(w.to(dev), bits, base_thresholds=base)
+    words = words.cpu().numpy()
+    np.testing.assert_array_equal(scale.cpu().numpy(), s)
+    np.testing.assert_array_equal(unpack_weight(words, cout, cin, kh, kw, bits), lv)
+    for copy in weight_copies(words, cout, cin, kh, kw, bits):
+        np.testing.assert_array_equal(copy, lv)
+    np.testing.assert_array_equal(weight_copy_f16(words, cout, cin, kh, kw, bits), lv)
+
+
 # packed outputs of pooled layers on every block shape: 256 rows x 128 and x 64
 # channels and the split-K shape, ragged channels, 255 windows an image
 @pytest.mark.parametrize("bits", [1, 2, 3])
