@@ -781,8 +781,8 @@ int qnet_layer_kernel(const qnet* net, int layer, int batch, char* buf, int len)
     snprintf(name, sizeof(name), "%s", (l.k == 3 && l.stride == 2 && l.pad == 1 && si.w % 2 == 0)
                                            ? "maxpool3s2_f32_kernel" : "maxpool_f32_kernel");
   } else if (l.kind == L_QUANTIZE) {
-    snprintf(name, sizeof(name), pack_act_by_pixel(batch, si.h, si.w) ? "pack_act_lds_kernel<%d>"
-                                                                                         : "pack_act_chan_kernel<%d>",
+    snprintf(name, sizeof(name),
+             pack_act_by_pixel(batch, si.c, si.h, si.w) ? "pack_act_lds_kernel<%d>" : "pack_act_chan_kernel<%d>",
              l.out_bits);
   } else if (l.kind == L_AVGPOOL) {
     snprintf(name, sizeof(name), "%s", si.h * si.w <= 60 ? "avgpool_lds_kernel" : "avgpool_f32_kernel");

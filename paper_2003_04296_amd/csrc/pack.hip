@@ -24,9 +24,9 @@ __device__ __forceinline__ uint32_t chan_mask(int remaining) {
 // Activations: a unit is one 32-channel word of 64 consecutive pixels (pixels
 // run over all images), computed by one wave with a pixel per lane: each
 // channel is read as one run of 256 bytes, 16 channels in flight before the
-// first compare.  A block holds the words of `sub` x 64 pixels, one wave per
-// unit, in LDS and writes them as one contiguous run.  Channels past 512 (16
-// words) go to further blocks, whose pixels' words are then runs of 64 P bytes.
+// first compare.  A block holds `group` words of `sub` x 64 pixels, one wave
+// per unit, in LDS and writes each pixel's as one run; where they are all of
+// its words the block's whole output is one run.
 // Bound by reading fp32 from HBM; measured on 1 / 2 / 3 bits with inputs not
 // in cache: 256 x 64 x 56 x 56 37.7 / 40.6 / 45.0 us (5.1-5.6 TB/s), 256 x 512
 // x 8 x 8 8.3 / 8.7 / 9.8 us, where waves that looped over whole pixel runs
@@ -73,18 +73,23 @@ struct WordBits {
 // lanes whose pixels lie a multiple of 32 words apart in different banks.
 __device__ __forceinline__ int tile_slot(int i) { return i + (i >> 5); }
 
-constexpr int PACK_GROUP = 16;  // words per pixel of a block
-
 template <int BITS>
 __global__ __launch_bounds__(1024) void pack_act_lds_kernel(const float* __restrict__ x, int c, int hw, int cwn,
-                                                            int groups, int npix, int sub, Thr t, int vec_out,
-                                                            uint32_t* __restrict__ out) {
+                                                            int groups, int group, int npix, int sub, Thr t,
+                                                            int vec_out, uint32_t* __restrict__ out) {
   constexpr int P = planes_of(BITS);
   extern __shared__ uint32_t tile[];  // [sub * 64][gw][P], padded by tile_slot
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int pb = groups == 1 ? blockIdx.x : blockIdx.x / groups;
-  const int cw0 = (blockIdx.x - pb * groups) * PACK_GROUP;
-  const int gw = min(cwn - cw0, PACK_GROUP);  // this block's words per pixel
+  int pb = blockIdx.x, cw0 = 0;  // run of pixels, first word
+  if (groups > 1) {
+    // the groups of a run on one XCD (blocks go to the 8 XCDs in turn), whose
+    // L2 then joins their pieces of a pixel's words; past the last run: exit
+    const int k = pb >> 3, q = k / groups;
+    cw0 = (k - q * groups) * group;
+    pb = q * 8 + (pb & 7);
+    if (pb * sub * 64 >= npix) return;
+  }
+  const int gw = min(cwn - cw0, group);  // this block's words per pixel
   const int pix0 = pb * sub * 64;
   const int sb = wave / gw, cwl = wave - sb * gw;
   if (sb < sub) {
@@ -586,10 +591,15 @@ __global__ __launch_bounds__(256) void pack_weight_f16_kernel(const float* __res
 }  // namespace
 
 // Lanes along the pixels where a wave's 64 pixels span at most five images (a
-// channel is then read in runs of 64 bytes and more), else along the channels
-// (256 x 1024 x 1 x 1 at 1 bit: 2.5 us, with lanes along the pixels 29.7 us).
-bool pack_act_by_pixel(int n, int h, int w) {
-  return (int64_t)h * w >= 16 && (int64_t)n * h * w < ((int64_t)1 << 31) - 1024;
+// channel is then read in runs of 64 bytes and more), and on smaller maps from
+// 4 pixels on where that still fills the chip, else along the channels.  Both
+// at 1 bit, pixels / channels: 256 x 512 x 3 x 5 3.5 / 10.9 us, 16 x 512 x 3 x
+// 5 3.6 / 2.6, 1024 x 128 x 2 x 4 2.9 / 4.2, 64 x 512 x 3 x 3 3.9 / 2.9, 16384
+// x 32 x 1 x 7 5.1 / 13.6, 1024 x 512 x 2 x 2 5.9 / 5.4, 65536 x 64 x 1 x 1
+// 10.8 / 8.4, 256 x 1024 x 1 x 1 29.7 / 2.5.
+bool pack_act_by_pixel(int n, int c, int h, int w) {
+  const int64_t hw = (int64_t)h * w, npix = n * hw, pairs = npix * ceil_div(ceil_div(c, 32), 2);
+  return npix < ((int64_t)1 << 31) - 1024 && (hw >= 16 || (hw >= 8 && pairs >= 8192) || (hw >= 4 && pairs >= 65536));
 }
 
 int launch_pack_act(const float* x, int n, int c, int h, int w, int bits, Thr t, uint32_t* out,
@@ -598,19 +608,31 @@ int launch_pack_act(const float* x, int n, int c, int h, int w, int bits, Thr t,
   const int cwn = ceil_div(c, 32);
   const int64_t npix = (int64_t)n * hw;
   if (npix == 0) return QCONV_OK;
-  if (pack_act_by_pixel(n, h, w)) {
-    // waves per block: one per word of 64 pixels while the tensor has fewer
-    // such runs than four per CU, else at least four, and eight where it has
-    // more than eight per CU (256 x 128 x 32 x 32 at 1 bit: 25.9 -> 24.9 us)
+  if (pack_act_by_pixel(n, c, h, w)) {
+    // Up to 16 words a block takes all of a pixel's, with one wave per word of
+    // 64 pixels while the tensor has fewer such runs than four per CU, else at
+    // least four waves, and two runs (8 to 16 waves) for 4 to 8 words where it
+    // has more than eight per CU (256 x 128 x 32 x 32 at 1 bit: 25.9 -> 24.9
+    // us).  Wider tensors, and maps below 16 pixels, whose runs are few, take
+    // groups of four words.  At 1 bit, inputs in cache / not, against one block
+    // per 64 pixels of an image and against groups of 16 words: 32 x 640 x 32 x
+    // 32 13.5 / 16.0 us (13.5 / 18.1; 15.9 / 20.0), 64 x 544 x 28 x 28 19.5 /
+    // 22.3 (22.4 / 25.2; 27.7 / 30.4), 128 x 1024 x 14 x 14 21.2 / 23.5 (24.2 /
+    // 27.7; 25.2 / 27.1), 512 x 640 x 7 x 7 13.8 / 15.3 (11.9 / 17.4; 20.7 /
+    // 23.1); 256 x 512 x 3 x 5 3.5 (5.2; 6.6).
     const int64_t runs = npix / 64;
-    const int sub = runs < 1024 ? 1 : (cwn < 4 ? ceil_div(4, cwn) : (cwn <= 8 && runs >= 2048 ? 2 : 1));
-    const int groups = ceil_div(cwn, PACK_GROUP), gw = cwn < PACK_GROUP ? cwn : PACK_GROUP;
-    const dim3 g((unsigned)((npix + sub * 64 - 1) / (sub * 64) * groups));
-    const int threads = 64 * sub * gw;
-    const size_t words = (size_t)sub * 64 * gw * planes_of(bits);
+    const bool split = cwn > 16 || hw < 16;
+    const int sub = split ? (hw < 16 ? 1 : 2)
+                          : (runs < 1024 ? 1 : (cwn < 4 ? ceil_div(4, cwn) : (cwn <= 8 && runs >= 2048 ? 2 : 1)));
+    const int group = split && cwn > 4 ? 4 : cwn, groups = ceil_div(cwn, group);
+    const int64_t blocks = (npix + sub * 64 - 1) / (sub * 64);
+    const dim3 g((unsigned)(groups == 1 ? blocks : (blocks + 7) / 8 * 8 * groups));
+    const int threads = 64 * sub * group;
+    const size_t words = (size_t)sub * 64 * group * planes_of(bits);
     const size_t lds = (words + words / 32) * sizeof(uint32_t);
     const int vec_out = ((uintptr_t)out & 15u) == 0;
-#define QC_PACK(B) pack_act_lds_kernel<B><<<g, threads, lds, s>>>(x, c, hw, cwn, groups, (int)npix, sub, t, vec_out, out)
+#define QC_PACK(B) \
+  pack_act_lds_kernel<B><<<g, threads, lds, s>>>(x, c, hw, cwn, groups, group, (int)npix, sub, t, vec_out, out)
     if (bits == 1) QC_PACK(1);
     else if (bits == 2) QC_PACK(2);
     else QC_PACK(3);
@@ -646,7 +668,7 @@ int launch_pack_act_f16(const float* x, int n, int c, int h, int w, uint32_t* ou
   const int64_t npix = (int64_t)n * hw, total = npix * cwn;
   if (total == 0) return QCONV_OK;
   // through LDS where lanes run along the pixels and every CU gets four waves
-  if (pack_act_by_pixel(n, h, w) && total >= 64 * 1024) {
+  if (hw >= 16 && npix < ((int64_t)1 << 31) - 1024 && total >= 64 * 1024) {
     const int groups = ceil_div(cwn, F16_GROUP), gw = cwn < F16_GROUP ? cwn : F16_GROUP;
     const dim3 g((unsigned)((npix + 63) / 64 * groups));
     pack_act_f16_lds_kernel<<<g, 64 * gw, 64 * (gw * 16 + 4) * sizeof(uint32_t), s>>>(

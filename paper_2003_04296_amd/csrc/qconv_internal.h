@@ -254,7 +254,7 @@ __host__ __device__ constexpr int act_words(int bits) { return bits == 16 ? 16 :
 // Launchers (each returns a qconv_status; inputs already validated).
 // ---------------------------------------------------------------------------
 // Whether launch_pack_act runs pack_act_lds_kernel (else pack_act_chan_kernel).
-bool pack_act_by_pixel(int n, int h, int w);
+bool pack_act_by_pixel(int n, int c, int h, int w);
 int launch_pack_act(const float* x, int n, int c, int h, int w, int bits, Thr t, uint32_t* out,
                     hipStream_t s);
 int launch_pack_act_f16(const float* x, int n, int c, int h, int w, uint32_t* out, hipStream_t s);

@@ -34,6 +34,11 @@ def _x(seed, shape):
 # on), ragged words, more than 16 words per pixel, and 1 / 2 / 4 runs per block
 PACK_SHAPES = [(5, 70, 3, 5), (9, 64, 1, 1), (3, 33, 4, 4), (2, 513, 4, 5), (1, 1000, 9, 8), (2, 36, 15, 13),
                (66, 64, 32, 32), (131, 100, 32, 32), (66, 20, 32, 31)]
+# small maps on both sides of where lanes run along the pixels (8192 pairs of
+# words from 8 pixels on, 65536 from 4 on), in groups of four words with a last
+# one of fewer; groups whose last run of pixels, and last eight runs, are not full
+PACK_SHAPES += [(1023, 40, 2, 4), (1024, 40, 2, 4), (911, 150, 3, 3), (16383, 20, 2, 2), (16385, 20, 2, 2),
+                (5500, 140, 1, 4), (9, 530, 13, 14), (1, 544, 45, 23), (37, 1030, 4, 4)]
 
 
 @pytest.mark.parametrize("bits", [1, 2, 3])
