@@ -170,7 +170,8 @@ typedef enum {
                               form applies (1-2 bit operands, 1x1 or 3x3,
                               stride <= 2, unpacked unpooled outputs) and
                               the layer has over 1024 tiles of 32 output
-                              pixels x 32 channels                          */
+                              pixels x 32 channels (over 768 for int32
+                              outputs of 1-bit weights with cin <= 128, 1x1) */
   QCONV_ALGO_BITPLANE = 1, /* VALU XNOR/AND + popcount over bitplanes         */
   QCONV_ALGO_MFMA_I8 = 2,  /* int8 matrix cores on the expanded level codes   */
   QCONV_ALGO_MFMA_FP4 = 3, /* fp4 (E2M1) matrix cores on the same codes; they

@@ -94,6 +94,17 @@ bool lat_applies(const ConvArgs& a) {
   return lat_plan(a, 1, &m);
 }
 
+// Whether AUTO prefers it to the XNOR kernel (contractions of up to 256
+// values).  It does except for int32 outputs of 1-bit weights in one or two
+// k-steps, where the XNOR kernel is as fast from about 768 tiles on (128 -> 256,
+// 28 x 28 / 2, 784 tiles: XNOR 6.1 us, this kernel 6.5; 592 tiles 6.0 and 5.3;
+// with batch norm 784 tiles 7.0 and 6.6, with 2-bit weights 7.1 and 6.5, and
+// 256 -> 256, four k-steps, 14 x 14, 784 tiles 7.0 and 6.6).
+bool lat_beats_xnor(const ConvArgs& a) {
+  if (!lat_applies(a)) return false;
+  return !(a.mode == QCONV_EPI_INT32 && a.w_bits == 1 && lat_steps(a) <= 2 && lat_tiles(a) > 768);
+}
+
 int lat_kernel_name(const ConvArgs& a, char* buf, int len) {
   int nt, sk;
   lat_shape(a, &nt, &sk);

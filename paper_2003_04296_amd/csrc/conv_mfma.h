@@ -1841,6 +1841,7 @@ __global__ __launch_bounds__(1024, 1) void conv_mfma_pp_kernel(const MfmaArgs m)
 
 // The kernel of layers with few output tiles (conv_lat.h, conv_lat.hip).
 bool lat_applies(const ConvArgs& a);
+bool lat_beats_xnor(const ConvArgs& a);
 int lat_kernel_name(const ConvArgs& a, char* buf, int len);
 int launch_conv_lat(const ConvArgs& a, hipStream_t s);
 

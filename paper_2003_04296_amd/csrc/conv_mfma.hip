@@ -291,7 +291,7 @@ bool use_pp(const MfmaArgs& m, int cfg, int cus) {
 
 using namespace mfma;
 
-bool mfma_is_small(const ConvArgs& a) { return lat_applies(a); }
+bool mfma_is_small(const ConvArgs& a) { return lat_beats_xnor(a); }
 
 bool mfma_supports(const ConvArgs& a) {
   if (a.stride > 2 || a.n == 0) return false;

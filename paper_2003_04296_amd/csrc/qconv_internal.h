@@ -300,8 +300,9 @@ int launch_conv_xnor(const ConvArgs& a, hipStream_t s);
 int xnor_kernel_name(const ConvArgs& a, char* buf, int len);
 int launch_conv_mfma(const ConvArgs& a, hipStream_t s);
 bool mfma_supports(const ConvArgs& a);
-// Whether the matrix-core layer has few output tiles (conv_lat.h): AUTO then
-// takes it whatever the contraction's size.
+// Whether the matrix-core layer has few output tiles, so that its kernel for
+// them (conv_lat.h) beats the XNOR kernel: AUTO then takes it whatever the
+// contraction's size.
 bool mfma_is_small(const ConvArgs& a);
 // Name of the kernel instantiation each launcher would run (template
 // arguments as the profiler prints them); returns the name's length.

@@ -232,6 +232,45 @@ def test_few_output_tiles(dev, case, ab, wb):
                                       oracle.quantize(oracle.hardtanh(zr), 3))
 
 
+# AUTO on contractions of up to 256 values: the few-tiles kernel up to 1024 tiles
+# (768 for int32 outputs of 1-bit weights in one or two k-steps), the XNOR kernel
+# past them, with the same values
+AUTO_CASES = [
+    # n, cin, h, w, cout, k, stride, pad, kernel of int32 outputs (1-bit, 2-bit weights), of the others
+    (24, 64, 16, 16, 128, 1, 1, 0, "lat", "lat", "lat"),
+    (25, 64, 16, 16, 128, 1, 1, 0, "xnor", "lat", "lat"),
+    (25, 160, 16, 16, 128, 1, 1, 0, "lat", "lat", "lat"),
+    (32, 64, 32, 32, 128, 1, 2, 0, "xnor", "lat", "lat"),
+    (33, 64, 32, 32, 128, 1, 2, 0, "xnor", "xnor", "xnor"),
+    (32, 28, 16, 16, 128, 3, 1, 1, "lat", "lat", "lat"),
+    (33, 28, 16, 16, 128, 3, 1, 1, "xnor", "xnor", "xnor"),
+]
+
+
+@pytest.mark.parametrize("ab, wb", [(1, 1), (2, 1), (2, 2), (1, 2)])
+@pytest.mark.parametrize("case", AUTO_CASES)
+def test_auto_small_contraction(dev, case, ab, wb):
+    n, cin, h, w, cout, k, s, p, int1, int2, other = case
+    geo = (n, cin, h, w, cout, k, s, p, ab, wb)
+    x = _x(42 + n, (n, cin, h, w))
+    g = synth.generator(43 + cin)
+    wt = synth.normal(g, (cout, cin, k, k), 2.0 / (k * k * cin))
+    kk, bb = synth.uniform(g, (cout,), 0.001, 0.05), synth.normal(g, (cout,), 0.1)
+    algo = {"lat": q.ALGO_MFMA_FP4, "xnor": q.ALGO_BITPLANE}
+    for mode, kernel in ((q.EPI_INT32, int1 if wb == 1 else int2), (q.EPI_SCALE_F32, other), (q.EPI_BN_F32, other)):
+        assert q.resolve_algo(*geo, mode=mode) == algo[kernel]
+        assert kernel in q.kernel_name(*geo, mode=mode)
+    act = q.pack_act(x.to(dev), ab)
+    wq, _ = q.pack_weight(wt.to(dev), wb)
+    lw, _ = oracle.quantize_weights(wt.numpy(), wb)
+    acc = oracle.qconv_acc(oracle.quantize(x.numpy(), ab), lw, ab, s, p)
+    out, _ = q.conv(act, wq, *geo)
+    np.testing.assert_array_equal(out.cpu().numpy(), acc)
+    out, _ = q.conv(act, wq, *geo, mode=q.EPI_BN_F32, bn_k=kk.to(dev), bn_b=bb.to(dev))
+    z = oracle.epi_bn(acc, kk.numpy(), bb.numpy(), oracle.level_shift(ab) + oracle.level_shift(wb))
+    np.testing.assert_array_equal(out.cpu().numpy(), z)
+
+
 # fp16 operands: the weight ring of 3 x 3 layers on both 256-row shapes, with one
 # and two words per stage (whole small images, runs of one image), a last stage
 # of one word, and the layers beside it (another kernel size)
