@@ -177,6 +177,14 @@ LAT_CASES = [
     (7, 128, 28, 28, 128, 1, 2, 0, (1, 4)),
     (32, 96, 32, 32, 32, 1, 1, 0, (1, 4)),
     (33, 96, 32, 32, 32, 3, 1, 1, None),
+    # both sides of two channel tiles (over 320 tiles and 10000 tile steps)
+    (80, 256, 8, 8, 64, 3, 1, 1, (1, 4)),
+    (81, 256, 8, 8, 64, 3, 1, 1, (2, 8)),
+    (138, 128, 8, 8, 64, 3, 1, 1, (1, 4)),
+    (139, 128, 8, 8, 64, 3, 1, 1, (2, 8)),
+    # and of 40000 tile steps
+    (222, 320, 8, 8, 64, 3, 1, 1, (2, 8)),
+    (223, 320, 8, 8, 64, 3, 1, 1, None),
 ]
 
 
