@@ -1261,15 +1261,18 @@ __global__ __launch_bounds__(256, blocks_per_cu(OPK, CFG)) void conv_mfma_kernel
                 acc[i][j] = mfma<OPK>(Acur[i], bf[j], acc[i][j]);
             }
         };
-        // fp16 operands and 3 x 3 kernels: the weights of E k-steps are loaded
-        // together, two groups ahead, and no step has a branch, so a group's
-        // loads have the MFMAs of 2 E k-steps to arrive under, where the loop
-        // below has one and a branch per step: 512 x 7 x 7 batch 256 with
+        // fp16 operands, a number of k-steps that 3 E divides (3 x 3 kernels, and
+        // 1 x 1 ones of 48, 96 or 192 channels): the weights of E k-steps are
+        // loaded together, two groups ahead, and no step has a branch, so a
+        // group's loads have the MFMAs of 2 E k-steps to arrive under, where the
+        // loop below has one and a branch per step: 512 x 7 x 7 batch 256 with
         // 16-bit weights 115 -> 100 us (0.59 PFLOP/s), 256 x 14 x 14 81 -> 68.5
-        // us.  E = 2 where the registers allow; the 128-channel shape of 16-bit
-        // inputs has none for it (it spilled 105 of them).
+        // us; 1 x 1, 28 x 28 batch 256, 192 -> 128 59.7 -> 53.7, 96 -> 64 30.5 ->
+        // 27.4.  E = 2 where the registers allow; the 128-channel shape has none
+        // for it with 16-bit inputs (105 spilled) or 3-bit ones (96 to 705: 384 ->
+        // 512, 1 x 1, 14 x 14 batch 256 134 us, the loop below 59.5).
         constexpr int E = MT == 4 ? 1 : 2;
-        constexpr bool RING3 = OPK == OP_F16 && SK == 1 && !(PA == 16 && MT == 4);
+        constexpr bool RING3 = OPK == OP_F16 && SK == 1 && !(PA >= 4 && MT == 4);
         if (RING3 && spc % E == 0 && nsteps_all % (3 * E) == 0) {
           v4i Bg[3][E][NT];
           int q_tap = 0, q_ksl = 0;
