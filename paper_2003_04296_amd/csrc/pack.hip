@@ -21,12 +21,13 @@ __device__ __forceinline__ uint32_t chan_mask(int remaining) {
   return remaining >= 32 ? 0xFFFFFFFFu : ((1u << remaining) - 1u);
 }
 
-// Activations: a unit is one 32-channel word of 64 consecutive pixels (pixels
-// run over all images), computed by one wave with a pixel per lane: each
-// channel is read as one run of 256 bytes, 16 channels in flight before the
-// first compare.  A block holds `group` words of `sub` x 64 pixels, one wave
-// per unit, in LDS and writes each pixel's as one run; where they are all of
-// its words the block's whole output is one run.
+// Activations: a unit is one 32-channel word of `run` (64, or the pixels of as
+// many whole images as fit in 64) consecutive pixels, counted over all images,
+// computed by one wave with a pixel per lane: each channel is read as one run
+// of 256 bytes, 16 channels in flight before the first compare.  A block holds
+// `group` words of `sub` runs, one wave per unit, in LDS and writes each
+// pixel's as one run; where they are all of its words the block's whole output
+// is one run.
 // Bound by reading fp32 from HBM; measured on 1 / 2 / 3 bits with inputs not
 // in cache: 256 x 64 x 56 x 56 37.7 / 40.6 / 45.0 us (5.1-5.6 TB/s), 256 x 512
 // x 8 x 8 8.3 / 8.7 / 9.8 us, where waves that looped over whole pixel runs
@@ -75,10 +76,10 @@ __device__ __forceinline__ int tile_slot(int i) { return i + (i >> 5); }
 
 template <int BITS>
 __global__ __launch_bounds__(1024) void pack_act_lds_kernel(const float* __restrict__ x, int c, int hw, int cwn,
-                                                            int groups, int group, int npix, int sub, Thr t,
-                                                            int vec_out, uint32_t* __restrict__ out) {
+                                                            int groups, int group, int npix, int sub, int run,
+                                                            Thr t, int vec_out, uint32_t* __restrict__ out) {
   constexpr int P = planes_of(BITS);
-  extern __shared__ uint32_t tile[];  // [sub * 64][gw][P], padded by tile_slot
+  extern __shared__ uint32_t tile[];  // [sub * run][gw][P], padded by tile_slot
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int pb = blockIdx.x, cw0 = 0;  // run of pixels, first word
   if (groups > 1) {
@@ -87,21 +88,21 @@ __global__ __launch_bounds__(1024) void pack_act_lds_kernel(const float* __restr
     const int k = pb >> 3, q = k / groups;
     cw0 = (k - q * groups) * group;
     pb = q * 8 + (pb & 7);
-    if (pb * sub * 64 >= npix) return;
+    if (pb * sub * run >= npix) return;
   }
   const int gw = min(cwn - cw0, group);  // this block's words per pixel
-  const int pix0 = pb * sub * 64;
+  const int pix0 = pb * sub * run;
   const int sb = wave / gw, cwl = wave - sb * gw;
   if (sb < sub) {
-    const int pl0 = sb * 64 + lane;             // pixel within the block's run
-    const int pix = min(pix0 + pl0, npix - 1);  // past the end: the last pixel, never written
+    const int pl0 = sb * run + min(lane, run - 1);  // pixel of the block (lanes past a run: its last one again)
+    const int pix = min(pix0 + pl0, npix - 1);      // past the end: the last pixel, never written
     const int b = (int)((uint32_t)pix / (uint32_t)hw);
     const int c0 = (cw0 + cwl) * 32, nch = min(32, c - c0);
     const float* src = x + ((int64_t)b * c + c0) * hw + (pix - b * hw);
     WordBits<BITS> wb;
     wb.clear();
     // NB channels from j0 up, every load issued before the first value is waited for
-    auto run = [&](auto NBC, int j0) __attribute__((always_inline)) {
+    auto read = [&](auto NBC, int j0) __attribute__((always_inline)) {
       constexpr int NB = decltype(NBC)::value;
       float v[NB];
 #pragma unroll
@@ -111,10 +112,10 @@ __global__ __launch_bounds__(1024) void pack_act_lds_kernel(const float* __restr
       for (int j = NB - 1; j >= 0; --j) wb.push(v[j], t);
     };
     if (nch == 32) {
-      run(std::integral_constant<int, 16>{}, 16);
-      run(std::integral_constant<int, 16>{}, 0);
+      read(std::integral_constant<int, 16>{}, 16);
+      read(std::integral_constant<int, 16>{}, 0);
     } else {
-      for (int j0 = (nch - 1) & ~3; j0 >= 0; j0 -= 4) run(std::integral_constant<int, 4>{}, j0);
+      for (int j0 = (nch - 1) & ~3; j0 >= 0; j0 -= 4) read(std::integral_constant<int, 4>{}, j0);
     }
     uint32_t pl[P];
     wb.planes(chan_mask(nch), pl);
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(1024) void pack_act_lds_kernel(const float* __restr
     for (int p = 0; p < P; ++p) tile[tile_slot((pl0 * gw + cwl) * P + p)] = pl[p];
   }
   __syncthreads();
-  const int nwords = min(sub * 64, npix - pix0) * gw * P;
+  const int nwords = min(sub * run, npix - pix0) * gw * P;
   if (groups > 1) {
     uint32_t* dst = out + ((int64_t)pix0 * cwn + cw0) * P;
     for (int i = threadIdx.x; i < nwords; i += blockDim.x) {
@@ -207,32 +208,35 @@ __global__ __launch_bounds__(256) void pack_act_f16_kernel(const float* __restri
   for (int q = 0; q < 4; ++q) dst[q] = make_uint4(h[4 * q], h[4 * q + 1], h[4 * q + 2], h[4 * q + 3]);
 }
 
-// The same through LDS: a block owns 64 consecutive pixels (over all images)
-// x up to F16_GROUP words, one wave per word with all its channels' loads in
-// flight, and writes each pixel's words as one run.  The direct kernel above
-// stores 16 bytes per lane 64 bytes and more apart.  Bound by HBM: 256 x 128 x
-// 32 x 32 46.1 -> 38.9 us (5.2 TB/s read + write), 256 x 64 x 56 x 56 66.1 ->
-// 56.4 us; 4 x 128 x 32 x 32, too few blocks, 3.0 -> 3.7 us.
-constexpr int F16_GROUP = 8;
+// The same through LDS: a block owns `sub` x 64 consecutive pixels (over all
+// images) x `group` words, one wave per word of 64 pixels with all its channels'
+// loads in flight, and writes each pixel's words as one run.  The direct kernel
+// above stores 16 bytes per lane 64 bytes and more apart.  Bound by HBM.
+// Inputs in cache / not, against the direct kernel: 256 x 128 x 32 x 32 30.1 /
+// 39.3 us (34.2 / 46.6), 256 x 64 x 56 x 56 52.2 / 57.9 (61.3 / 67.6); 4 x 128 x
+// 32 x 32, too few blocks, 3.7 in cache (3.0).
 __global__ __launch_bounds__(512) void pack_act_f16_lds_kernel(const float* __restrict__ x, int c, int hw, int cwn,
-                                                               int groups, int npix, uint4* __restrict__ out) {
-  extern __shared__ __attribute__((aligned(16))) uint32_t tile[];  // [64][16 gw + 4]
+                                                               int groups, int group, int sub, int npix,
+                                                               uint4* __restrict__ out) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t tile[];  // [sub * 64][16 gw + 4]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int pb = groups == 1 ? blockIdx.x : blockIdx.x / groups;
-  const int cw0 = (blockIdx.x - pb * groups) * F16_GROUP;
-  const int gw = min(cwn - cw0, F16_GROUP);
+  const int cw0 = (blockIdx.x - pb * groups) * group;
+  const int gw = min(cwn - cw0, group);
   const int pitch = gw * 16 + 4;  // 4 words of padding: lanes' 16-byte writes fall in different banks
-  const int pix0 = pb * 64;
-  if (wave < gw) {
-    const int pix = min(pix0 + lane, npix - 1);
+  const int pix0 = pb * sub * 64;
+  const int sb = wave / gw, cwl = wave - sb * gw;
+  if (sb < sub) {
+    const int pl0 = sb * 64 + lane;
+    const int pix = min(pix0 + pl0, npix - 1);
     const int b = (int)((uint32_t)pix / (uint32_t)hw);
-    const int c0 = (cw0 + wave) * 32, nch = min(32, c - c0);
+    const int c0 = (cw0 + cwl) * 32, nch = min(32, c - c0);
     const float* src = x + ((int64_t)b * c + c0) * hw + (pix - b * hw);
     float v[32];
 #pragma unroll
     for (int j = 0; j < 32; ++j) v[j] = src[(int64_t)min(j, nch - 1) * hw];
     __builtin_amdgcn_sched_barrier(0);  // every load is issued before the first value is waited for
-    uint4* dst = reinterpret_cast<uint4*>(tile + lane * pitch + wave * 16);
+    uint4* dst = reinterpret_cast<uint4*>(tile + pl0 * pitch + cwl * 16);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       uint32_t h[4];
@@ -246,7 +250,7 @@ __global__ __launch_bounds__(512) void pack_act_f16_lds_kernel(const float* __re
     }
   }
   __syncthreads();
-  const int row = gw * 4, n4 = min(64, npix - pix0) * row;
+  const int row = gw * 4, n4 = min(sub * 64, npix - pix0) * row;
   uint4* dst = out + ((int64_t)pix0 * cwn + cw0) * 4;
   for (int i = threadIdx.x; i < n4; i += blockDim.x) {
     const int px = i / row, r = i - px * row;
@@ -591,15 +595,18 @@ __global__ __launch_bounds__(256) void pack_weight_f16_kernel(const float* __res
 }  // namespace
 
 // Lanes along the pixels where a wave's 64 pixels span at most five images (a
-// channel is then read in runs of 64 bytes and more), and on smaller maps from
-// 4 pixels on where that still fills the chip, else along the channels.  Both
-// at 1 bit, pixels / channels: 256 x 512 x 3 x 5 3.5 / 10.9 us, 16 x 512 x 3 x
-// 5 3.6 / 2.6, 1024 x 128 x 2 x 4 2.9 / 4.2, 64 x 512 x 3 x 3 3.9 / 2.9, 16384
-// x 32 x 1 x 7 5.1 / 13.6, 1024 x 512 x 2 x 2 5.9 / 5.4, 65536 x 64 x 1 x 1
-// 10.8 / 8.4, 256 x 1024 x 1 x 1 29.7 / 2.5.
+// channel is then read in runs of 64 bytes and more), on smaller maps from 4
+// pixels on where that still fills the chip, and from 2 on up to 8 channels,
+// which leave most lanes along them idle; else along the channels.  Both at 1 bit,
+// pixels / channels: 256 x 512 x 3 x 5 3.5 / 10.9 us, 16 x 512 x 3 x 5 3.6 /
+// 2.6, 1024 x 128 x 2 x 4 2.9 / 4.2, 64 x 512 x 3 x 3 3.9 / 2.9, 16384 x 32 x 1
+// x 7 5.1 / 13.6, 1024 x 512 x 2 x 2 5.9 / 5.4, 65536 x 64 x 1 x 1 10.8 / 8.4,
+// 256 x 1024 x 1 x 1 29.7 / 2.5; 2000 x 3 x 2 x 2 3.0 / 3.6, 141 x 8 x 3 x 4 3.0
+// / 3.2, 141 x 16 x 3 x 4 3.4 / 3.2.
 bool pack_act_by_pixel(int n, int c, int h, int w) {
   const int64_t hw = (int64_t)h * w, npix = n * hw, pairs = npix * ceil_div(ceil_div(c, 32), 2);
-  return npix < ((int64_t)1 << 31) - 1024 && (hw >= 16 || (hw >= 8 && pairs >= 8192) || (hw >= 4 && pairs >= 65536));
+  return npix < ((int64_t)1 << 31) - 1024 &&
+         (hw >= 16 || (hw >= 2 && c <= 8) || (hw >= 8 && pairs >= 8192) || (hw >= 4 && pairs >= 65536));
 }
 
 int launch_pack_act(const float* x, int n, int c, int h, int w, int bits, Thr t, uint32_t* out,
@@ -609,30 +616,48 @@ int launch_pack_act(const float* x, int n, int c, int h, int w, int bits, Thr t,
   const int64_t npix = (int64_t)n * hw;
   if (npix == 0) return QCONV_OK;
   if (pack_act_by_pixel(n, c, h, w)) {
-    // Up to 16 words a block takes all of a pixel's, with one wave per word of
-    // 64 pixels while the tensor has fewer such runs than four per CU, else at
-    // least four waves, and two runs (8 to 16 waves) for 4 to 8 words where it
-    // has more than eight per CU (256 x 128 x 32 x 32 at 1 bit: 25.9 -> 24.9
-    // us).  Wider tensors, and maps below 16 pixels, whose runs are few, take
-    // groups of four words.  At 1 bit, inputs in cache / not, against one block
-    // per 64 pixels of an image and against groups of 16 words: 32 x 640 x 32 x
-    // 32 13.5 / 16.0 us (13.5 / 18.1; 15.9 / 20.0), 64 x 544 x 28 x 28 19.5 /
-    // 22.3 (22.4 / 25.2; 27.7 / 30.4), 128 x 1024 x 14 x 14 21.2 / 23.5 (24.2 /
-    // 27.7; 25.2 / 27.1), 512 x 640 x 7 x 7 13.8 / 15.3 (11.9 / 17.4; 20.7 /
-    // 23.1); 256 x 512 x 3 x 5 3.5 (5.2; 6.6).
-    const int64_t runs = npix / 64;
-    const bool split = cwn > 16 || hw < 16;
-    const int sub = split ? (hw < 16 ? 1 : 2)
-                          : (runs < 1024 ? 1 : (cwn < 4 ? ceil_div(4, cwn) : (cwn <= 8 && runs >= 2048 ? 2 : 1)));
-    const int group = split && cwn > 4 ? 4 : cwn, groups = ceil_div(cwn, group);
-    const int64_t blocks = (npix + sub * 64 - 1) / (sub * 64);
+    // How many words (group) and runs (sub) a block takes.  At 1 bit, inputs in
+    // cache / not, against one block per 64 pixels of an image:
+    // - Maps of 16 to 63 pixels that do not divide 64: runs of whole images,
+    //   which are then read from a few whole cache lines where a run of 64
+    //   pixels reads parts of lines of two images, in groups of four words: 935
+    //   x 512 x 7 x 7 15.7 / 19.3 us (15.6 / 21.5; runs of 64 23.7 / 25.0), 512
+    //   x 640 x 7 x 7 11.7 / 14.0 (12.6 / 19.6; 17.0 / 18.0), 675 x 256 x 6 x 6
+    //   5.1 / 7.0 (5.8 / 9.2; 6.4 / 8.0).  (The limit keeps a launch of such
+    //   runs, up to 64 lanes for 33 pixels, below 2^32 threads.)
+    // - Larger maps whose planes are not whole runs of 64 bytes: two words of
+    //   four consecutive runs, which share the cache lines at their ends, where
+    //   that leaves one wave per SIMD: 195 x 512 x 11 x 11 at 2 bits 11.7 / 13.7
+    //   (13.8 / 17.9; all 16 words of one run 14.7 / 16.0), 900 x 128 x 9 x 9
+    //   8.8 / 11.0 (11.3 / 11.9; 11.7 / 12.0).
+    // - Else up to 16 words all of a pixel's, with one wave per word of a run
+    //   while the tensor has fewer runs than four per CU, else at least four
+    //   waves, and two runs (8 to 16 waves) for 4 to 8 words where it has more
+    //   than eight per CU (256 x 128 x 32 x 32 25.9 -> 24.9 us).
+    // - More words, and maps below 16 pixels, whose runs are few: groups of
+    //   four.  32 x 640 x 32 x 32 13.5 / 16.0 us (13.5 / 18.1; groups of 16
+    //   15.9 / 20.0), 64 x 544 x 28 x 28 19.5 / 22.3 (22.4 / 25.2; 27.7 / 30.4),
+    //   128 x 1024 x 14 x 14 21.2 / 23.5 (24.2 / 27.7; 25.2 / 27.1); 256 x 512 x
+    //   3 x 5 3.5 (5.2; 6.6).
+    const int run = hw >= 16 && hw < 64 && npix * cwn < ((int64_t)1 << 31) ? 64 / hw * hw : 64;
+    const int64_t runs = npix / run;
+    int group = cwn, sub = 1;
+    if (hw < 16) group = cwn < 4 ? cwn : 4;
+    else if (cwn < 4) sub = runs < 1024 ? 1 : ceil_div(4, cwn);
+    else if (run < 64) group = 4;
+    else if (cwn > 16) group = 4, sub = 2;
+    else if (hw % 16 && runs * cwn >= 1024) group = 2, sub = 4;
+    else if (cwn <= 8 && runs >= 2048) sub = 2;
+    const int groups = ceil_div(cwn, group);
+    const int64_t blocks = (npix + sub * run - 1) / (sub * run);
     const dim3 g((unsigned)(groups == 1 ? blocks : (blocks + 7) / 8 * 8 * groups));
     const int threads = 64 * sub * group;
-    const size_t words = (size_t)sub * 64 * group * planes_of(bits);
+    const size_t words = (size_t)sub * run * group * planes_of(bits);
     const size_t lds = (words + words / 32) * sizeof(uint32_t);
-    const int vec_out = ((uintptr_t)out & 15u) == 0;
+    // every block's output starts on 16 bytes
+    const int vec_out = ((uintptr_t)out & 15u) == 0 && (sub * run * cwn * planes_of(bits)) % 4 == 0;
 #define QC_PACK(B) \
-  pack_act_lds_kernel<B><<<g, threads, lds, s>>>(x, c, hw, cwn, groups, group, (int)npix, sub, t, vec_out, out)
+  pack_act_lds_kernel<B><<<g, threads, lds, s>>>(x, c, hw, cwn, groups, group, (int)npix, sub, run, t, vec_out, out)
     if (bits == 1) QC_PACK(1);
     else if (bits == 2) QC_PACK(2);
     else QC_PACK(3);
@@ -669,10 +694,17 @@ int launch_pack_act_f16(const float* x, int n, int c, int h, int w, uint32_t* ou
   if (total == 0) return QCONV_OK;
   // through LDS where lanes run along the pixels and every CU gets four waves
   if (hw >= 16 && npix < ((int64_t)1 << 31) - 1024 && total >= 64 * 1024) {
-    const int groups = ceil_div(cwn, F16_GROUP), gw = cwn < F16_GROUP ? cwn : F16_GROUP;
-    const dim3 g((unsigned)((npix + 63) / 64 * groups));
-    pack_act_f16_lds_kernel<<<g, 64 * gw, 64 * (gw * 16 + 4) * sizeof(uint32_t), s>>>(
-        x, c, hw, cwn, groups, (int)npix, reinterpret_cast<uint4*>(out));
+    // up to eight words of one run of 64 pixels; of maps whose planes are not
+    // whole runs of 64 bytes two words (or all three) of two consecutive runs or
+    // a single one of four, which share the cache lines at their ends (451 x 256 x 6 x 6 6.4 / 7.5 us,
+    // the direct kernel 6.4 / 8.9, eight words 7.3 / 8.0; 416 x 32 x 44 x 47 27.2
+    // / 32.9, 29.1 / 36.2, one run 31.6 / 33.8)
+    const bool shared = hw % 16 != 0;
+    const int group = shared ? (cwn <= 3 ? cwn : 2) : (cwn < 8 ? cwn : 8), sub = shared ? (cwn == 1 ? 4 : 2) : 1;
+    const int groups = ceil_div(cwn, group);
+    const dim3 g((unsigned)((npix + sub * 64 - 1) / (sub * 64) * groups));
+    pack_act_f16_lds_kernel<<<g, 64 * group * sub, (size_t)sub * 64 * (group * 16 + 4) * sizeof(uint32_t), s>>>(
+        x, c, hw, cwn, groups, group, sub, (int)npix, reinterpret_cast<uint4*>(out));
     return hip_status();
   }
   pack_act_f16_kernel<<<dim3((unsigned)((total + 255) / 256)), 256, 0, s>>>(x, c, hw, cwn, total, out);

@@ -39,6 +39,11 @@ PACK_SHAPES = [(5, 70, 3, 5), (9, 64, 1, 1), (3, 33, 4, 4), (2, 513, 4, 5), (1, 
 # one of fewer; groups whose last run of pixels, and last eight runs, are not full
 PACK_SHAPES += [(1023, 40, 2, 4), (1024, 40, 2, 4), (911, 150, 3, 3), (16383, 20, 2, 2), (16385, 20, 2, 2),
                 (5500, 140, 1, 4), (9, 530, 13, 14), (1, 544, 45, 23), (37, 1030, 4, 4)]
+# runs of whole images (fewer than 64 pixels, several small images or one, a last
+# group of words that is not full, more than 16 words), two words of four runs
+# from 1024 (run, word) pairs on, and up to 8 channels on maps of 2 pixels and more
+PACK_SHAPES += [(19, 150, 7, 7), (3, 70, 5, 5), (701, 40, 5, 7), (2100, 36, 3, 11), (7, 520, 6, 6), (1, 130, 7, 9),
+                (80, 290, 9, 9), (91, 290, 9, 9), (141, 3, 1, 2), (77, 8, 3, 4), (77, 9, 3, 4)]
 
 
 @pytest.mark.parametrize("bits", [1, 2, 3])
@@ -67,9 +72,11 @@ def test_pack_act_many_images(dev):
     assert (out[n:] == 0x5A5A5A5A).all()
 
 
-# through LDS from 65536 (pixel, word) pairs on (here 2 and 9 words per
-# pixel), directly below
-@pytest.mark.parametrize("shape", [(33, 40, 32, 32), (8, 270, 31, 31), (3, 40, 9, 9)])
+# through LDS from 65536 (pixel, word) pairs on (here up to 10 words per pixel, in
+# groups of 8 of one run of pixels and, where a plane is not whole runs of 64
+# bytes, of 1 to 3 of four or two), directly below
+@pytest.mark.parametrize("shape", [(33, 40, 32, 32), (8, 270, 31, 31), (3, 40, 9, 9), (9, 300, 28, 28), (700, 70, 6, 6),
+                                   (61, 20, 33, 35)])
 def test_pack_act16(dev, shape):
     n, c, h, w = shape
     x = _x(32, shape)
