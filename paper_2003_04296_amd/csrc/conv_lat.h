@@ -129,7 +129,7 @@ __global__ __launch_bounds__(64 * SK) void conv_mfma_lat_kernel(const MfmaArgs m
     const int to = (ky * a.w + kx) * apix;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
-      voff[i] = ((rmask[i] >> ky) & (cmask[i] >> kx) & 1u) ? base[i] + to : 0x7FFFFFF0;
+      voff[i] = ((rmask[i] >> ky) & (cmask[i] >> kx) & 1u) ? base[i] + to : OFF_NONE;
   };
   tap_offsets();
   uint32_t ra[D][MT][PA];
@@ -193,13 +193,13 @@ __global__ __launch_bounds__(64 * SK) void conv_mfma_lat_kernel(const MfmaArgs m
     const int pc = wk + SK * k;  // piece: tile pc / 4, rows pc % 4
     const int ti = (pc >> 2) / NT, tj = (pc >> 2) - ti * NT, q = pc & 3;
     const int co = co_blk + 32 * tj + r32;
-    const int cvo = co < a.cout ? co * 4 : 0x7FFFFFF0;
+    const int cvo = co < a.cout ? co * 4 : OFF_NONE;
     kv[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(krsrc, cvo, 0, 0));
     bv[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(prsrc, cvo, 0, 0));
     const int u = (T0 + ti) * TU + (POOL ? q + 4 * g : 8 * q + 4 * g);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      oo[k][i] = 0x7FFFFFF0;
+      oo[k][i] = OFF_NONE;
       rv[k][i] = 0.0f;
     }
     if (a.mode != QCONV_EPI_BN_PACK) {  // uniform
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(64 * SK) void conv_mfma_lat_kernel(const MfmaArgs m
       for (int i = 0; i < NV; ++i) {
         const int img = (int)fdiv((uint32_t)(u + i), m.fd_upi);
         const bool ok = u + i < total && co < a.cout;
-        oo[k][i] = ok ? ((img * a.cout + co) * m.upi + (u + i - img * m.upi)) * 4 : 0x7FFFFFF0;
+        oo[k][i] = ok ? ((img * a.cout + co) * m.upi + (u + i - img * m.upi)) * 4 : OFF_NONE;
         rv[k][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rrsrc, oo[k][i], 0, 0));
       }
     }

@@ -53,7 +53,7 @@ bool lat_plan(const ConvArgs& a, int nt, MfmaArgs* m) {
   m->inv = 1.0f / (float)(1 << a.shift);
   m->othr = thr_unclamped(a.othr);
   const int64_t ob = (int64_t)a.n * a.cout * m->upi * 4;
-  if (a.mode != QCONV_EPI_BN_PACK && ob >= ((int64_t)1 << 31)) return false;
+  if (a.mode != QCONV_EPI_BN_PACK && ob > OFF_NONE) return false;
   m->out_bytes = a.mode == QCONV_EPI_BN_PACK ? 0 : (int)ob;
   return true;
 }

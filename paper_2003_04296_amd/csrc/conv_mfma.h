@@ -158,12 +158,16 @@ struct MfmaArgs {
   int halo_bytes;
   float inv;          // 2^-shift
   Thr othr;           // requantization thresholds for |z| (HardTanh folded in, thr_unclamped)
-  int out_bytes;      // byte size of the unpacked output (buffer-resource bound, < 2^31)
+  int out_bytes;      // byte size of the unpacked output (buffer-resource bound; 0 if past OFF_NONE)
   int buf_bytes;      // LDS bytes of one halo buffer
   int grid;           // blocks launched (each loops over the work items)
   int direct;         // the unstaged form (direct_body): units run over all images, 256 per block
-  int act_bytes;      // byte size of the packed activations (buffer-resource bound; 0 if >= 2^31)
+  int act_bytes;      // byte size of the packed activations (buffer-resource bound; 0 if past OFF_NONE)
 };
+
+// The byte offset of lanes that have no element: loads there return 0 and
+// stores are dropped, so a buffer reached with it ends at or before it.
+constexpr int OFF_NONE = 0x7FFFFFF0;
 
 // One 32 x 32 MFMA of operand format OPK on 16-byte fragments.
 template <int OPK, class AccT>
@@ -454,7 +458,7 @@ __device__ __forceinline__ void swap_res_load(const MfmaArgs& m, int img0, int u
   const int g = lane >> 5, r32 = lane & 31;
   int img, uu;
   const bool uok = unit_of(m, img0, u0, 32 * T + r32, &img, &uu);
-  const int voff = uok ? (int)((((int64_t)img * a.cout + co32 + 4 * g) * m.upi + uu) * 4) : 0x7FFFFFF0;
+  const int voff = uok ? (int)((((int64_t)img * a.cout + co32 + 4 * g) * m.upi + uu) * 4) : OFF_NONE;
   const __amdgpu_buffer_rsrc_t rrsrc =
       __builtin_amdgcn_make_buffer_rsrc((void*)a.residual, (short)0, m.out_bytes, 0x00020000);
   const int pstride = m.upi * 4;
@@ -518,7 +522,7 @@ __device__ __forceinline__ void tile_epilogue_swap(const MfmaArgs& m, const AccT
   } else {
     int img, uu;
     unit_of(m, img0, u0, t, &img, &uu);
-    const int voff = uok ? (int)((((int64_t)img * a.cout + cbase) * m.upi + uu) * 4) : 0x7FFFFFF0;
+    const int voff = uok ? (int)((((int64_t)img * a.cout + cbase) * m.upi + uu) * 4) : OFF_NONE;
     const __amdgpu_buffer_rsrc_t orsrc =
         __builtin_amdgcn_make_buffer_rsrc(a.out, (short)0, m.out_bytes, 0x00020000);
     const int pstride = m.upi * 4;
@@ -537,7 +541,7 @@ __device__ __forceinline__ void tile_epilogue_swap(const MfmaArgs& m, const AccT
       auto put = [&](int v, uint32_t bits) __attribute__((always_inline)) {
         const int c = 8 * (v / 4) + v % 4;
         if constexpr (PERM) {
-          const int vo = decltype(FULL)::value || cbase + c < a.cout ? voff : 0x7FFFFFF0;
+          const int vo = decltype(FULL)::value || cbase + c < a.cout ? voff : OFF_NONE;
           __builtin_amdgcn_raw_buffer_store_b32(bits, orsrc, vo, c * pstride, 0);
         } else {
           if (full || cbase + c < a.cout) __builtin_amdgcn_raw_buffer_store_b32(bits, orsrc, voff, c * pstride, 0);
@@ -1030,7 +1034,7 @@ __device__ __forceinline__ void direct_body(const MfmaArgs& m, Epi&& epi) {
       (void*)(bn ? a.bn_k : a.scale), (short)0, a.mode == QCONV_EPI_INT32 ? 0 : a.cout * 4, 0x00020000);
   const __amdgpu_buffer_rsrc_t prsrc =
       __builtin_amdgcn_make_buffer_rsrc((void*)a.bn_b, (short)0, bn ? a.cout * 4 : 0, 0x00020000);
-  const int pvoff = tid < BCO ? (co_blk + tid) * 4 : 0x7FFFFFF0;
+  const int pvoff = tid < BCO ? (co_blk + tid) * 4 : OFF_NONE;
   const uint32_t pk = __builtin_amdgcn_raw_buffer_load_b32(krsrc, pvoff, 0, 0);
   const uint32_t pb = __builtin_amdgcn_raw_buffer_load_b32(prsrc, pvoff, 0, 0);
   // byte offset of each row's first tap word (this lane's k-half; may lie
@@ -1063,7 +1067,7 @@ __device__ __forceinline__ void direct_body(const MfmaArgs& m, Epi&& epi) {
     const int to = (ky * a.w + kx) * apix;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
-      voff[i] = ((rmask[i] >> ky) & (cmask[i] >> kx) & 1u) ? base[i] + to : 0x7FFFFFF0;
+      voff[i] = ((rmask[i] >> ky) & (cmask[i] >> kx) & 1u) ? base[i] + to : OFF_NONE;
   };
   tap_offsets();
   uint32_t ra[D][MT][PA];
@@ -1476,7 +1480,7 @@ __device__ __forceinline__ void load_halo_rsrc(const MfmaArgs& m, __amdgpu_buffe
     const int img = img0 + slot;
     const int iy = iy0 + hrow, ix = hcol - a.pad;
     const bool ok = it < items && img < a.n && iy >= 0 && iy < a.h && ix >= 0 && ix < a.w && cw < a.cw;
-    const int off = ok ? (((img * a.h + iy) * a.w + ix) * apix + cw * PA) * 4 : 0x7FFFFFF0;
+    const int off = ok ? (((img * a.h + iy) * a.w + ix) * apix + cw * PA) * 4 : OFF_NONE;
     if constexpr (PA == 1) {
       raw[u][0] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, off, 0, 0);
     } else if constexpr (PA == 2) {

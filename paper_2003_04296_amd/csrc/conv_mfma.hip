@@ -126,9 +126,9 @@ bool plan(const ConvArgs& a, int cfg, MfmaArgs* m) {
   m->inv = 1.0f / (float)(1 << a.shift);
   m->othr = thr_unclamped(a.othr);
   const int64_t ab = (int64_t)a.n * a.h * a.w * a.cw * act_words(a.a_bits) * 4;
-  m->act_bytes = ab < ((int64_t)1 << 31) ? (int)ab : 0;
+  m->act_bytes = ab <= OFF_NONE ? (int)ab : 0;
   const int64_t ob = (int64_t)a.n * a.cout * m->upi * 4;
-  m->out_bytes = ob < ((int64_t)1 << 31) ? (int)ob : 0;
+  m->out_bytes = ob <= OFF_NONE ? (int)ob : 0;
   m->buf_bytes = (m->halo_bytes + 15) & ~15;
   if (cfg == 2) m->buf_bytes = max(m->buf_bytes, RED_BYTES / 2);  // the two buffers hold the split-K partials
   return true;
@@ -194,8 +194,8 @@ bool direct_applies(const ConvArgs& a, MfmaArgs* m) {
   const int64_t wxb = (int64_t)a.kh * a.kw * ksteps * a.cop * 32;
   const int64_t ab = (int64_t)a.n * a.h * a.w * a.cw * act_words(a.a_bits) * 4;
   const int64_t ob = units * a.cout * 4;
-  // buffer offsets past the end stay below 2^31; exact fast divisions
-  if (wxb >= ((int64_t)1 << 30) || ab >= ((int64_t)1 << 30) || ob >= ((int64_t)1 << 31) ||
+  // no buffer reaches OFF_NONE; exact fast divisions
+  if (wxb >= ((int64_t)1 << 30) || ab >= ((int64_t)1 << 30) || ob > OFF_NONE ||
       (units + 256) * upi >= ((int64_t)1 << 32) || upi * a.wo >= ((int64_t)1 << 32))
     return false;
   memset(m, 0, sizeof(*m));

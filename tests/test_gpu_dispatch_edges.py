@@ -372,6 +372,37 @@ def test_unstaged_form(dev, case, ab, wb):
                                       oracle.quantize(oracle.hardtanh(zr), ob))
 
 
+# Buffers of 2147483640 bytes: lanes without an element use the byte offset
+# 2147483632 of a buffer resource, which lies inside such a buffer.  An output of
+# that size (its last group of 32 pixels has one): no such lane may store into
+# it; inputs of that size: the pixels outside an image are 0.
+@pytest.mark.parametrize("ab, algo", [(1, q.ALGO_MFMA_FP4), (3, q.ALGO_MFMA_FP4), (2, q.ALGO_MFMA_I8)])
+def test_output_past_the_masked_offset(dev, ab, algo):
+    n, cin, h, w, cout = 4859, 64, 15, 29, 254
+    assert n * cout * h * w * 4 == 2147483640
+    g = torch.Generator(device=dev).manual_seed(50)
+    x = torch.randn((n, cin, h, w), generator=g, device=dev)
+    wq, _ = q.pack_weight(torch.randn((cout, cin, 3, 3), generator=g, device=dev), 1)
+    out, _ = q.conv(q.pack_act(x, ab), wq, n, cin, h, w, cout, 3, 1, 1, ab, 1, algo=algo)
+    for i0, m in ((0, 3), (n // 2, 40), (n - 50, 50)):  # the same images in small batches
+        part, _ = q.conv(q.pack_act(x[i0:i0 + m].contiguous(), ab), wq, m, cin, h, w, cout, 3, 1, 1, ab, 1, algo=algo)
+        assert torch.equal(out[i0:i0 + m], part)
+
+
+def test_input_past_the_masked_offset(dev):
+    n, h, w, cout = 18705, 113, 127, 1
+    assert q.packed_act_words(n, 1, h, w, 2) * 4 == 2147483640
+    g = torch.Generator(device=dev).manual_seed(51)
+    x = torch.randn((n, 1, h, w), generator=g, device=dev)
+    x.view(-1)[-8:] = 2.0  # the words at the offset: nonzero levels
+    wq, _ = q.pack_weight(torch.randn((cout, 1, 3, 3), generator=g, device=dev), 1)
+    geo = (1, h, w, cout, 3, 1, 1, 2, 1)
+    out, _ = q.conv(q.pack_act(x, 2), wq, n, *geo, algo=q.ALGO_MFMA_FP4)
+    for i0, m in ((0, 40), (n - 40, 40)):
+        part, _ = q.conv(q.pack_act(x[i0:i0 + m].contiguous(), 2), wq, m, *geo, algo=q.ALGO_MFMA_FP4)
+        assert torch.equal(out[i0:i0 + m], part)
+
+
 # the last FC reads operands 16 inputs (fp32) or half a word (packed signs)
 # ahead: odd and even numbers of groups, remainders, one chunk and several
 @pytest.mark.parametrize("inputs", [3, 15, 16, 17, 32, 47, 64, 95, 192, 208, 223, 1024, 1056, 1071])
