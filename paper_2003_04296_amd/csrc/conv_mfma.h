@@ -161,9 +161,14 @@ struct MfmaArgs {
   int out_bytes;      // byte size of the unpacked output (buffer-resource bound; 0 if past OFF_NONE)
   int buf_bytes;      // LDS bytes of one halo buffer
   int grid;           // blocks launched (each loops over the work items)
-  int direct;         // the unstaged form (direct_body): units run over all images, 256 per block
+  int form;           // which kernel (FORM_*)
   int act_bytes;      // byte size of the packed activations (buffer-resource bound; 0 if past OFF_NONE)
 };
+
+// The kernels of a matrix-core layer: conv_mfma_kernel, the store-overlapped
+// conv_mfma_pp_kernel, its unstaged form (direct_body: units run over all images,
+// 256 per block), and conv_mfma_lat_kernel (conv_lat.h).
+enum Form { FORM_BASE = 0, FORM_PP = 1, FORM_DIRECT = 2, FORM_LAT = 3 };
 
 // The byte offset of lanes that have no element: loads there return 0 and
 // stores are dropped, so a buffer reached with it ends at or before it.
@@ -1568,7 +1573,7 @@ __global__ __launch_bounds__(1024, 1) void conv_mfma_pp_kernel(const MfmaArgs m)
   extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
   const ConvArgs& a = m.c;
   if constexpr (OPK == OP_FP4 && CFG == 1 && PA <= 2) {
-    if (m.direct) {  // uniform over the launch (blocks of 256 threads)
+    if (m.form == FORM_DIRECT) {  // uniform over the launch (blocks of 256 threads)
       direct_body<PA, 2>(m, [&](const v16f (&acc)[2][2], int T0, int co, const float* prm, int lane)
                                 __attribute__((always_inline)) {
         Unroll<0, 4>::run([&](auto TT) __attribute__((always_inline)) {
@@ -1855,8 +1860,6 @@ int launch_conv_lat(const ConvArgs& a, hipStream_t s);
 // Host-side planning (conv_mfma.hip).
 int device_cus();
 bool use_swap(const MfmaArgs& m);
-bool use_pp(const MfmaArgs& m, int cfg, int cus);
-bool direct_applies(const ConvArgs& a, MfmaArgs* m);
 size_t pp_lds(const MfmaArgs& m, int cfg);
 size_t block_lds(const MfmaArgs& m);
 constexpr int LDS_PER_CU = 160 * 1024;
@@ -1881,13 +1884,12 @@ bool raise_lds_limit_of(size_t bytes) {
 template <int OPK, int PA, int CFG>
 int launch_cfg(MfmaArgs m, hipStream_t s) {
   if constexpr (OPK == OP_FP4 && CFG == 1 && PA <= 2) {
-    MfmaArgs dm;
-    if (direct_applies(m.c, &dm)) {
-      const dim3 grid((unsigned)(dm.tiles_px * dm.tiles_co));
+    if (m.form == FORM_DIRECT) {
+      const dim3 grid((unsigned)(m.tiles_px * m.tiles_co));
       if (m.c.out_packed)  // PA planes: the input's width, as direct_applies asks
-        conv_mfma_pp_kernel<OPK, PA, CFG, PA><<<grid, 256, PARAM_BYTES, s>>>(dm);
+        conv_mfma_pp_kernel<OPK, PA, CFG, PA><<<grid, 256, PARAM_BYTES, s>>>(m);
       else
-        conv_mfma_pp_kernel<OPK, PA, CFG, 0><<<grid, 256, PARAM_BYTES, s>>>(dm);
+        conv_mfma_pp_kernel<OPK, PA, CFG, 0><<<grid, 256, PARAM_BYTES, s>>>(m);
       return hip_status();
     }
   }
@@ -1895,7 +1897,7 @@ int launch_cfg(MfmaArgs m, hipStream_t s) {
   const int total = m.tiles_px * m.tiles_co;
   const int cus = device_cus();
   if constexpr (CFG != 2 && OPK != OP_F16) {
-    if (use_pp(m, CFG, cus)) {
+    if (m.form == FORM_PP) {
       const size_t plds = pp_lds(m, CFG);
       // every block keeps one output-channel tile: a multiple of tiles_co blocks
       m.grid = max(m.tiles_co, (min(total, cus) / m.tiles_co) * m.tiles_co);

@@ -200,7 +200,7 @@ bool direct_applies(const ConvArgs& a, MfmaArgs* m) {
     return false;
   memset(m, 0, sizeof(*m));
   m->c = a;
-  m->direct = 1;
+  m->form = FORM_DIRECT;
   m->ksteps = ksteps;
   m->wx = a.w_fp4;
   m->wx_bytes = (int)wxb;
@@ -224,10 +224,9 @@ bool direct_applies(const ConvArgs& a, MfmaArgs* m) {
 // are enough (its epilogue then runs beside the other group's MFMAs instead
 // of after them).
 int pick_cfg(const ConvArgs& a) {
-  MfmaArgs m0, m1;
-  if (direct_applies(a, &m0) && plan(a, 1, &m1)) return 1;  // (the shape of its name)
   const int cfg = pick_cfg_base(a);
   if (cfg != 0) return cfg;
+  MfmaArgs m0, m1;
   const int cus = device_cus();
   if (plan(a, 0, &m0) && !use_pp(m0, 0, cus) && plan(a, 1, &m1) && use_pp(m1, 1, cus)) return 1;
   return 0;
@@ -286,7 +285,24 @@ bool use_pp(const MfmaArgs& m, int cfg, int cus) {
   return true;
 }
 
-
+// The kernel that runs a layer (m->form) with its block shape and arguments,
+// for the launch and for its name; false: none serves it.  (The unstaged form
+// and the few-tiles kernel have no input tile in LDS, but are not asked for more
+// layers than the kernels that do: the tile of the 64-channel shape, for the
+// few-tiles kernel of any shape, has to fit.)
+bool choose(const ConvArgs& a, int* cfg, MfmaArgs* m) {
+  if (a.stride > 2 || a.n < 1) return false;
+  MfmaArgs d;
+  if (direct_applies(a, &d) && plan(a, 1, m)) {
+    *cfg = 1;
+    *m = d;
+    return true;
+  }
+  *cfg = pick_cfg(a);
+  if (!plan(a, *cfg, m)) return false;
+  m->form = lat_applies(a) ? FORM_LAT : (use_pp(*m, *cfg, device_cus()) ? FORM_PP : FORM_BASE);
+  return true;
+}
 }  // namespace mfma
 
 using namespace mfma;
@@ -294,34 +310,33 @@ using namespace mfma;
 bool mfma_is_small(const ConvArgs& a) { return lat_beats_xnor(a); }
 
 bool mfma_supports(const ConvArgs& a) {
-  if (a.stride > 2 || a.n == 0) return false;
+  int cfg;
   MfmaArgs m;
-  return plan(a, pick_cfg(a), &m);
+  return choose(a, &cfg, &m);
 }
 
 int mfma_kernel_name(const ConvArgs& a, char* buf, int len) {
+  int cfg;
   MfmaArgs m;
-  const int cfg = pick_cfg(a);
-  if (!plan(a, cfg, &m)) return QCONV_EUNSUPPORTED;
+  if (!choose(a, &cfg, &m)) return QCONV_EUNSUPPORTED;
   char name[96];
-  MfmaArgs d;
-  if (lat_applies(a))
+  if (m.form == FORM_LAT)
     lat_kernel_name(a, name, (int)sizeof(name));
-  else if (direct_applies(a, &d) || use_pp(m, cfg, device_cus()))
-    snprintf(name, sizeof(name), "conv_mfma_pp_kernel<%d, %d, %d, %d>", a.mfma_op, act_words(a.a_bits), cfg,
-             a.out_packed ? a.out_bits : 0);
-  else
+  else if (m.form == FORM_BASE)
     snprintf(name, sizeof(name), "conv_mfma_kernel<%d, %d, %d, %d>", a.mfma_op, act_words(a.a_bits), cfg,
              use_swap(m) ? 1 : 0);
+  else
+    snprintf(name, sizeof(name), "conv_mfma_pp_kernel<%d, %d, %d, %d>", a.mfma_op, act_words(a.a_bits), cfg,
+             a.out_packed ? a.out_bits : 0);
   if (buf && len > 0) snprintf(buf, (size_t)len, "%s", name);
   return (int)strlen(name);
 }
 
 int launch_conv_mfma(const ConvArgs& a, hipStream_t s) {
+  int cfg;
   MfmaArgs m;
-  const int cfg = pick_cfg(a);
-  if (!plan(a, cfg, &m)) return QCONV_EUNSUPPORTED;
-  if (lat_applies(a)) return launch_conv_lat(a, s);
+  if (!choose(a, &cfg, &m)) return QCONV_EUNSUPPORTED;
+  if (m.form == FORM_LAT) return launch_conv_lat(a, s);
   const int pa = act_words(a.a_bits);
   if (a.mfma_op == OP_F16) {
     if (pa == 16) return launch_mfma_f16_p16(m, cfg, s);

@@ -1,6 +1,8 @@
 """Edges of the kernel choices (run with -m gpu): shapes on both sides of each
 rule that picks a kernel or a block shape, against the CPU oracle.  Packed
 levels and integer accumulators are compared bit for bit."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -370,6 +372,42 @@ def test_unstaged_form(dev, case, ab, wb):
         np.testing.assert_array_equal(out.cpu().numpy(), zr)
         np.testing.assert_array_equal(unpack_act(outp.cpu().numpy()[:words], n, cout, ho, wo, ob),
                                       oracle.quantize(oracle.hardtanh(zr), ob))
+
+
+def _launched(fn):
+    """What fn returns, and the names of the library's kernels that it launched."""
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        r = fn()
+        torch.cuda.synchronize()
+    return r, [re.sub(r"^void qc::mfma::|\(qc::mfma::.*$", "", e.key) for e in prof.key_averages() if "qc::" in e.key]
+
+
+# A stride-2 layer of wide rows: the input tile of the 256-pixel shapes does not
+# fit from 147 columns on, and no kernel that is then not launched is named
+@pytest.mark.parametrize("w, kernel", [(146, "conv_mfma_pp_kernel<1, 2, 1, "), (147, "conv_mfma_kernel<1, 2, 2, 1>"),
+                                       (160, "conv_mfma_kernel<1, 2, 2, 1>")])
+def test_wide_rows(dev, w, kernel):
+    n, c = 16, 64
+    geo = (n, c, w, w, c, 3, 2, 1, 2, 2)
+    x = _x(52, (n, c, w, w))
+    g = synth.generator(53)
+    wt = synth.normal(g, (c, c, 3, 3), 2.0 / (9 * c))
+    kk, bb = synth.uniform(g, (c,), 0.001, 0.05), synth.normal(g, (c,), 0.1)
+    act = q.pack_act(x.to(dev), 2)
+    wq, _ = q.pack_weight(wt.to(dev), 2)
+    lw, _ = oracle.quantize_weights(wt.numpy(), 2)
+    acc = oracle.qconv_acc(oracle.quantize(x.numpy(), 2), lw, 2, 2, 1)
+    kw = dict(mode=q.EPI_BN_PACK, out_bits=2)
+    names = q.kernel_name(*geo), q.kernel_name(*geo, packed_out=True, **kw)
+    (out, _), ran = _launched(lambda: q.conv(act, wq, *geo))
+    assert ran == [names[0]] and names[0].startswith(kernel), (ran, names)
+    np.testing.assert_array_equal(out.cpu().numpy(), acc)
+    bn = kk.to(dev), bb.to(dev)
+    (_, outp), ran = _launched(lambda: q.conv(act, wq, *geo, bn_k=bn[0], bn_b=bn[1], **kw))
+    assert ran == [names[1]] and names[1].startswith(kernel), (ran, names)
+    z = oracle.epi_bn(acc, kk.numpy(), bb.numpy(), 2 * oracle.level_shift(2))
+    ho = q.out_size(w, 3, 2, 1)
+    np.testing.assert_array_equal(unpack_act(outp.cpu().numpy(), n, c, ho, ho, 2), oracle.quantize(oracle.hardtanh(z), 2))
 
 
 # Buffers of 2147483640 bytes: lanes without an element use the byte offset
