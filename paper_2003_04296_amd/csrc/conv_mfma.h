@@ -1129,14 +1129,25 @@ __device__ __forceinline__ void direct_body(const MfmaArgs& m, Epi&& epi) {
   epi(acc, T0, co_blk, prm, lane);
 }
 
+// The weight ring of fp16 operands (in conv_mfma_kernel): the shapes that have
+// it and its k-steps a group.
+constexpr bool ring_shape(int opk, int pa, int cfg) { return opk == OP_F16 && cfg != 2 && !(pa >= 4 && cfg == 0); }
+constexpr int ring_group(int cfg) { return cfg == 0 ? 1 : 2; }
+
 // The convolution kernel.  Blocks loop over work items (pixel tile x channel
 // tile) with a stride of the grid size.  Each (item, channel chunk) is a
 // stage; the packed words of stage s + 1 are loaded into registers before
 // the MFMAs of stage s and expanded into the other of two LDS halo buffers
 // after them, so that global latency, the expansion and the epilogue's
 // stores overlap the matrix work.  Split-K shapes run one item per block.
-template <int OPK, int PA, int CFG, int SWAP>
+// VAR: bit 0 the orientation (1: weights as the A operand, for unpacked unpooled
+// outputs), bit 1 the weight ring of fp16 layers (use_ring).  The ring is a form
+// of its own because the layers that cannot use it (few-step 1 x 1 ones) were
+// slower with its code in their kernel: 16-bit inputs, 64 -> 64, 28 x 28 batch 16
+// 10.5 -> 11.3 us.
+template <int OPK, int PA, int CFG, int VAR>
 __global__ __launch_bounds__(256, blocks_per_cu(OPK, CFG)) void conv_mfma_kernel(const MfmaArgs m) {
+  constexpr bool SWAP = VAR & 1;
   using O = OpT<OPK>;
   using acc_t = typename O::acc_t;
   using C = Cfg<CFG>;
@@ -1280,9 +1291,10 @@ __global__ __launch_bounds__(256, blocks_per_cu(OPK, CFG)) void conv_mfma_kernel
         // 27.4.  E = 2 where the registers allow; the 128-channel shape has none
         // for it with 16-bit inputs (105 spilled) or 3-bit ones (96 to 705: 384 ->
         // 512, 1 x 1, 14 x 14 batch 256 134 us, the loop below 59.5).
-        constexpr int E = MT == 4 ? 1 : 2;
-        constexpr bool RING3 = OPK == OP_F16 && SK == 1 && !(PA >= 4 && MT == 4);
-        if (RING3 && spc % E == 0 && nsteps_all % (3 * E) == 0) {
+        constexpr int E = ring_group(CFG);
+        constexpr bool RING = (VAR & 2) != 0;
+        static_assert(!RING || ring_shape(OPK, PA, CFG), "no weight ring in this shape");
+        if (RING && spc % E == 0 && nsteps_all % (3 * E) == 0) {  // (a last, shorter stage may take the loop)
           v4i Bg[3][E][NT];
           int q_tap = 0, q_ksl = 0;
           auto bgroup = [&](v4i (&dst)[E][NT]) __attribute__((always_inline)) {
@@ -1860,6 +1872,7 @@ int launch_conv_lat(const ConvArgs& a, hipStream_t s);
 // Host-side planning (conv_mfma.hip).
 int device_cus();
 bool use_swap(const MfmaArgs& m);
+bool use_ring(const MfmaArgs& m, int cfg);
 size_t pp_lds(const MfmaArgs& m, int cfg);
 size_t block_lds(const MfmaArgs& m);
 constexpr int LDS_PER_CU = 160 * 1024;
@@ -1879,6 +1892,13 @@ bool raise_lds_limit_of(size_t bytes) {
     return false;
   if (d) d->store((int)bytes, std::memory_order_relaxed);
   return true;
+}
+
+template <int OPK, int PA, int CFG, int VAR>
+int launch_var(const MfmaArgs& m, size_t lds, hipStream_t s) {
+  if (lds > 64 * 1024 && !raise_lds_limit_of<conv_mfma_kernel<OPK, PA, CFG, VAR>>(lds)) return QCONV_EHIP;
+  conv_mfma_kernel<OPK, PA, CFG, VAR><<<dim3((unsigned)m.grid), 256, lds, s>>>(m);
+  return hip_status();
 }
 
 template <int OPK, int PA, int CFG>
@@ -1929,14 +1949,11 @@ int launch_cfg(MfmaArgs m, hipStream_t s) {
     const int per_cu = max(1, min(blocks_per_cu(OPK, CFG), (int)(LDS_PER_CU / lds)));
     m.grid = min(total, per_cu * cus);
   }
-  if (use_swap(m)) {
-    if (lds > 64 * 1024 && !raise_lds_limit_of<conv_mfma_kernel<OPK, PA, CFG, 1>>(lds)) return QCONV_EHIP;
-    conv_mfma_kernel<OPK, PA, CFG, 1><<<dim3((unsigned)m.grid), 256, lds, s>>>(m);
-  } else {
-    if (lds > 64 * 1024 && !raise_lds_limit_of<conv_mfma_kernel<OPK, PA, CFG, 0>>(lds)) return QCONV_EHIP;
-    conv_mfma_kernel<OPK, PA, CFG, 0><<<dim3((unsigned)m.grid), 256, lds, s>>>(m);
+  if constexpr (ring_shape(OPK, PA, CFG)) {
+    if (use_ring(m, CFG))
+      return use_swap(m) ? launch_var<OPK, PA, CFG, 3>(m, lds, s) : launch_var<OPK, PA, CFG, 2>(m, lds, s);
   }
-  return hip_status();
+  return use_swap(m) ? launch_var<OPK, PA, CFG, 1>(m, lds, s) : launch_var<OPK, PA, CFG, 0>(m, lds, s);
 }
 
 template <int OPK, int PA>

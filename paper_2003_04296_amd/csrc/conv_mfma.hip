@@ -239,6 +239,13 @@ bool use_swap(const MfmaArgs& m) {
   return !a.pool && m.out_bytes > 0;
 }
 
+// Whether a stage's k-steps fill the rounds of three groups of the weight ring.
+bool use_ring(const MfmaArgs& m, int cfg) {
+  if (!ring_shape(m.c.mfma_op, act_words(m.c.a_bits), cfg)) return false;
+  const int e = ring_group(cfg), spc = min(m.ksteps, m.chunk_words * 32 / OpT<OP_F16>::K_PER_STEP);
+  return spc % e == 0 && (m.c.kh * m.c.kw * spc) % (3 * e) == 0;
+}
+
 // Compute units of the current device, queried once per device.
 int device_cus() {
   static std::atomic<int> cache[MAX_DEVICES];
@@ -324,7 +331,7 @@ int mfma_kernel_name(const ConvArgs& a, char* buf, int len) {
     lat_kernel_name(a, name, (int)sizeof(name));
   else if (m.form == FORM_BASE)
     snprintf(name, sizeof(name), "conv_mfma_kernel<%d, %d, %d, %d>", a.mfma_op, act_words(a.a_bits), cfg,
-             use_swap(m) ? 1 : 0);
+             (use_swap(m) ? 1 : 0) + (use_ring(m, cfg) ? 2 : 0));
   else
     snprintf(name, sizeof(name), "conv_mfma_pp_kernel<%d, %d, %d, %d>", a.mfma_op, act_words(a.a_bits), cfg,
              a.out_packed ? a.out_bits : 0);
