@@ -85,11 +85,22 @@ int launch_pa(const MfmaArgs& m, int nt, int sk, hipStream_t s) {
 // against 9.7 us, 784 of 9 (64 x 56 x 56 batch 4, the same) 7.7 against 8.2;
 // 1568 of 18 (128 x 28 x 28 batch 16) 12.5 against 10.1, 1568 of 36 (256 -> 512
 // / 2 batch 64, packed) 11.3 against 10.7.  Only with fp4 operands and where
-// the LDS-staged kernel serves the layer too.
+// the LDS-staged kernel serves the layer too.  Unpacked outputs of 3-bit inputs,
+// whose expansion is the longest, up to 512 tiles where a tile has more than 9
+// steps (128 -> 128, 14 x 14: 392 tiles 5.4 against 7.0 us, 588 7.4 against 7.2,
+// 784 7.9 against 7.3; packed 5.2 against 7.3).  Int32 and scaled outputs, whose
+// epilogue hides least of it, up to 768 tiles where a tile has 9 to 17 steps and
+// the split-K shape's 64 channels are used (64 -> 64 int32: 13 x 13 782 tiles 0.93
+// of its speed, 898 0.88, 38 x 38 904 0.90, 28 x 28 784 1.00, 56 x 56 784 1.03;
+// 32 -> 32 13 x 13 999 1.38; with batch norm 1.00 to 1.26).
 bool lat_applies(const ConvArgs& a) {
   if (a.mfma_op != OP_FP4 || a.stride > 2 || a.kh > 16 || a.kw > 16 || a.n < 1) return false;
   const int64_t tiles = lat_tiles(a);
   if (tiles < 1 || tiles > 1024 || tiles * lat_steps(a) > 40000) return false;
+  if (a.a_bits == 3 && tiles > 512 && lat_steps(a) > 9 && !a.pool && a.mode != QCONV_EPI_BN_PACK) return false;
+  if ((a.mode == QCONV_EPI_INT32 || a.mode == QCONV_EPI_SCALE_F32) && !a.pool && tiles > 768 && a.kreal > 256 &&
+      lat_steps(a) >= 9 && lat_steps(a) < 18 && (a.cout - 1) % 64 >= 32)
+    return false;
   MfmaArgs m;
   return lat_plan(a, 1, &m);
 }

@@ -194,6 +194,15 @@ LAT_CASES = [
     # and of 40000 tile steps
     (222, 320, 8, 8, 64, 3, 1, 1, (2, 8)),
     (223, 320, 8, 8, 64, 3, 1, 1, None),
+    # and of 512 tiles, where 3-bit inputs with unpacked outputs end
+    (128, 128, 8, 8, 64, 3, 1, 1, (1, 4)),
+    (129, 128, 8, 8, 64, 3, 1, 1, (1, 4)),
+    # and of 768 tiles, where int32 outputs of 9 to 17 steps end, and beside them
+    # another number of steps and 32 channels
+    (48, 64, 16, 16, 64, 3, 1, 1, (1, 4)),
+    (49, 64, 16, 16, 64, 3, 1, 1, None),
+    (49, 64, 16, 16, 64, 2, 1, 0, (1, 4)),
+    (97, 64, 16, 16, 32, 3, 1, 1, (1, 4)),
 ]
 
 
@@ -218,8 +227,12 @@ def test_few_output_tiles(dev, case, ab, wb):
         flags = q.EPI_POOL2 if pool else 0
         name = q.kernel_name(n, cin, h, w, cout, k, s, p, ab, wb, flags=flags, algo=algo)
         if not pool:
-            want = f"conv_mfma_lat_kernel<{q.planes(ab)}, {shape[0]}, {shape[1]}, 0>" if shape else "conv_mfma_kernel"
+            many = n * -(-ho * wo // 32) * -(-cout // 32) > 512  # (maps of whole tiles where it matters)
+            lat = shape and not (ab == 3 and many and k * k * -(-cin // 64) > 9)
+            want = f"conv_mfma_lat_kernel<{q.planes(ab)}, {shape[0]}, {shape[1]}, 0>" if lat else "conv_mfma_kernel"
             assert name.startswith(want), name
+            if (n, cin, k) == (49, 64, 3):  # batch norm and residual stay
+                assert "lat" in q.kernel_name(n, cin, h, w, cout, k, s, p, ab, wb, mode=q.EPI_BN_F32, algo=algo)
         a = acc
         if pool:
             oh, ow = ho // 2, wo // 2
