@@ -166,8 +166,9 @@ struct MfmaArgs {
 };
 
 // The kernels of a matrix-core layer: conv_mfma_kernel, the store-overlapped
-// conv_mfma_pp_kernel, its unstaged form (direct_body: units run over all images,
-// 256 per block), and conv_mfma_lat_kernel (conv_lat.h).
+// conv_mfma_pp_kernel, its unstaged form (CFG_DIRECT, direct_body: units run over
+// all images, 256 per block), and conv_mfma_lat_kernel (conv_lat.h).
+constexpr int CFG_DIRECT = 3;  // the unstaged form's place among the block shapes
 enum Form { FORM_BASE = 0, FORM_PP = 1, FORM_DIRECT = 2, FORM_LAT = 3 };
 
 // The byte offset of lanes that have no element: loads there return 0 and
@@ -1006,20 +1007,22 @@ __device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rsrc, int voff
 }
 
 // The unstaged form of the store-overlapped kernel's 64-channel shape (fp4,
-// 1- and 2-bit inputs): no tiles in LDS and no barrier, blocks of four
-// independent waves in place of two groups that take turns.  A wave owns 64
-// pixels (of all images, in order) x 64 channels; a lane reads the packed word
-// of its own pixels for each (tap, k-step), D steps ahead, expands it into its
-// operand fragment in registers and meets the weight fragments read the same
-// way, and one wave's epilogue and stores run under another's products.  Where
+// 1- and 2-bit inputs): no tiles in LDS, and blocks of four waves in place of two
+// groups that take turns.  A wave owns 64 pixels (of all images, in order) x 64
+// channels; a lane reads the packed word of its own pixels for each (tap,
+// k-step), D steps ahead, expands it into its operand fragment in registers and
+// meets the weight fragments read the same way.  The one barrier, for the
+// parameters in LDS, is after the products, so a block's waves start their
+// epilogues together; its stores run under the products of the CU's other
+// three blocks.  Where
 // a layer has few k-steps, the staged forms spend more on a block's weights,
 // halo tiles and barriers, and on the part of a 256-pixel item past the end of
 // an image, than these repeated expansions cost.  Measured at 2 bits (before:
 // the staged form): ResNet-18 batch 64, 64 x 56 x 56 with residual and packed
 // copy 31.6 -> 25.6 us, 128 x 28 x 28 the same 23.5 -> 18.6, 64 -> 128 / 2
-// packed 14.0 -> 9.0.  D = 2 and four waves a SIMD: with 3 or 4 steps ahead
-// and three waves the 64-channel layers measured 5-10 % slower, the deeper
-// ones 2-5 % faster; 3-bit inputs spill within 128 registers.
+// packed 14.0 -> 9.0.  D = 2 and four waves a SIMD (128 registers): with 3 or 4
+// steps ahead and three waves the 64-channel layers measured 5-10 % slower, the
+// deeper ones 2-5 % faster; 3-bit inputs spilled within 128 registers.
 template <int PA, int D, class Epi>
 __device__ __forceinline__ void direct_body(const MfmaArgs& m, Epi&& epi) {
   constexpr int MT = 2, NT = 2, WM = 4, BCO = 32 * NT;
@@ -1575,7 +1578,7 @@ constexpr int PP_GROUP = 512;  // threads per wave group
 // operand, so that a lane holds one channel); needs a single channel chunk
 // and packed activations below 2 GiB.
 template <int OPK, int PA, int CFG, int OB>
-__global__ __launch_bounds__(1024, 1) void conv_mfma_pp_kernel(const MfmaArgs m) {
+__device__ __forceinline__ void pp_body(const MfmaArgs& m) {
   using O = OpT<OPK>;
   using acc_t = typename O::acc_t;
   using C = PCfg<CFG>;
@@ -1584,30 +1587,6 @@ __global__ __launch_bounds__(1024, 1) void conv_mfma_pp_kernel(const MfmaArgs m)
   constexpr int NI = PA == 4 ? 2 : 3;  // halo items per thread held in registers
   extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
   const ConvArgs& a = m.c;
-  if constexpr (OPK == OP_FP4 && CFG == 1 && PA <= 2) {
-    if (m.form == FORM_DIRECT) {  // uniform over the launch (blocks of 256 threads)
-      direct_body<PA, 2>(m, [&](const v16f (&acc)[2][2], int T0, int co, const float* prm, int lane)
-                                __attribute__((always_inline)) {
-        Unroll<0, 4>::run([&](auto TT) __attribute__((always_inline)) {
-          constexpr int t = decltype(TT)::value;
-          const int co32 = co + 32 * (t % 2);
-          if (co32 >= a.cout) return;  // uniform
-          const v16f& A = acc[t / 2][t % 2];
-          const int T = T0 + t / 2;
-          if (a.mode == QCONV_EPI_INT32) {
-            tile_epilogue_swap<K_INT32, 0, 0, true>(m, A, 0, 0, T, co32, co, prm, lane);
-          } else if (a.mode == QCONV_EPI_SCALE_F32) {
-            tile_epilogue_swap<K_SCALE, 0, 0, true>(m, A, 0, 0, T, co32, co, prm, lane);
-          } else if (a.mode == QCONV_EPI_BN_PACK) {
-            if constexpr (OB > 0) tile_epilogue_swap<K_PACK, 0, OB, true>(m, A, 0, 0, T, co32, co, prm, lane);
-          } else {
-            tile_epilogue_swap<K_BNF32, 2, OB, true>(m, A, 0, 0, T, co32, co, prm, lane);
-          }
-        });
-      });
-      return;
-    }
-  }
   // wave-uniform indices in scalar registers
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave >> 3, wq = wave & 7;
@@ -1863,6 +1842,42 @@ __global__ __launch_bounds__(1024, 1) void conv_mfma_pp_kernel(const MfmaArgs m)
   }
 }
 
+// The unstaged form of the same layers (direct_body, above).
+template <int PA, int OB>
+__device__ __forceinline__ void unstaged(const MfmaArgs& m) {
+  const ConvArgs& a = m.c;
+  direct_body<PA, 2>(m, [&](const v16f (&acc)[2][2], int T0, int co, const float* prm, int lane)
+                            __attribute__((always_inline)) {
+    Unroll<0, 4>::run([&](auto TT) __attribute__((always_inline)) {
+      constexpr int t = decltype(TT)::value;
+      const int co32 = co + 32 * (t % 2);
+      if (co32 >= a.cout) return;  // uniform
+      const v16f& A = acc[t / 2][t % 2];
+      const int T = T0 + t / 2;
+      if (a.mode == QCONV_EPI_INT32) {
+        tile_epilogue_swap<K_INT32, 0, 0, true>(m, A, 0, 0, T, co32, co, prm, lane);
+      } else if (a.mode == QCONV_EPI_SCALE_F32) {
+        tile_epilogue_swap<K_SCALE, 0, 0, true>(m, A, 0, 0, T, co32, co, prm, lane);
+      } else if (a.mode == QCONV_EPI_BN_PACK) {
+        if constexpr (OB > 0) tile_epilogue_swap<K_PACK, 0, OB, true>(m, A, 0, 0, T, co32, co, prm, lane);
+      } else {
+        tile_epilogue_swap<K_BNF32, 2, OB, true>(m, A, 0, 0, T, co32, co, prm, lane);
+      }
+    });
+  });
+}
+
+// CFG_DIRECT: the unstaged form, in blocks of 256 threads and, as the staged
+// shapes, 128 registers (four waves a SIMD).
+template <int OPK, int PA, int CFG, int OB>
+__global__ __launch_bounds__(CFG == CFG_DIRECT ? 256 : 1024, CFG == CFG_DIRECT ? 4 : 1)
+void conv_mfma_pp_kernel(const MfmaArgs m) {
+  if constexpr (CFG == CFG_DIRECT)
+    unstaged<PA, OB>(m);
+  else
+    pp_body<OPK, PA, CFG, OB>(m);
+}
+
 // The kernel of layers with few output tiles (conv_lat.h, conv_lat.hip).
 bool lat_applies(const ConvArgs& a);
 bool lat_beats_xnor(const ConvArgs& a);
@@ -1903,16 +1918,6 @@ int launch_var(const MfmaArgs& m, size_t lds, hipStream_t s) {
 
 template <int OPK, int PA, int CFG>
 int launch_cfg(MfmaArgs m, hipStream_t s) {
-  if constexpr (OPK == OP_FP4 && CFG == 1 && PA <= 2) {
-    if (m.form == FORM_DIRECT) {
-      const dim3 grid((unsigned)(m.tiles_px * m.tiles_co));
-      if (m.c.out_packed)  // PA planes: the input's width, as direct_applies asks
-        conv_mfma_pp_kernel<OPK, PA, CFG, PA><<<grid, 256, PARAM_BYTES, s>>>(m);
-      else
-        conv_mfma_pp_kernel<OPK, PA, CFG, 0><<<grid, 256, PARAM_BYTES, s>>>(m);
-      return hip_status();
-    }
-  }
   const size_t lds = block_lds(m);
   const int total = m.tiles_px * m.tiles_co;
   const int cus = device_cus();
@@ -1958,6 +1963,16 @@ int launch_cfg(MfmaArgs m, hipStream_t s) {
 
 template <int OPK, int PA>
 int launch_fp(const MfmaArgs& m, int cfg, hipStream_t s) {
+  if constexpr (OPK == OP_FP4 && PA <= 2) {
+    if (cfg == CFG_DIRECT) {
+      const dim3 grid((unsigned)(m.tiles_px * m.tiles_co));
+      if (m.c.out_packed)  // PA planes: the input's width, as direct_applies asks
+        conv_mfma_pp_kernel<OPK, PA, CFG_DIRECT, PA><<<grid, 256, PARAM_BYTES, s>>>(m);
+      else
+        conv_mfma_pp_kernel<OPK, PA, CFG_DIRECT, 0><<<grid, 256, PARAM_BYTES, s>>>(m);
+      return hip_status();
+    }
+  }
   if (cfg == 0) return launch_cfg<OPK, PA, 0>(m, s);
   if (cfg == 1) return launch_cfg<OPK, PA, 1>(m, s);
   return launch_cfg<OPK, PA, 2>(m, s);

@@ -301,7 +301,7 @@ bool choose(const ConvArgs& a, int* cfg, MfmaArgs* m) {
   if (a.stride > 2 || a.n < 1) return false;
   MfmaArgs d;
   if (direct_applies(a, &d) && plan(a, 1, m)) {
-    *cfg = 1;
+    *cfg = CFG_DIRECT;
     *m = d;
     return true;
   }

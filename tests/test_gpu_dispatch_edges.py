@@ -329,10 +329,18 @@ def test_fp16_integer_values(dev, n, cin, h, cout, k, ab, wb):
     np.testing.assert_array_equal(out.cpu().numpy()[idx], want)
 
 
-# the unstaged form of the store-overlapped kernel (its 64-channel shape on 1- and
-# 2-bit inputs): ragged maps, channels and batches (a last block of a few
-# pixels, waves and channel tiles with nothing to do), strides, 1 x 1, one and
-# two k-steps a tap, and the layers beside its limits, on the staged kernels
+def _launched(fn):
+    """What fn returns, and the names of the library's kernels that it launched."""
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        r = fn()
+        torch.cuda.synchronize()
+    return r, [re.sub(r"^void qc::mfma::|\(qc::mfma::.*$", "", e.key) for e in prof.key_averages() if "qc::" in e.key]
+
+
+# the unstaged form of the store-overlapped kernel (1- and 2-bit inputs): ragged
+# maps, channels and batches (a last block of a few pixels, waves and channel
+# tiles with nothing to do), strides, 1 x 1, one and two k-steps a tap; and the
+# staged 64-channel shape on layers beside the unstaged form's limits
 DIRECT_CASES = [
     # n, cin, h, w, cout, k, stride, pad, packed output alone on it too
     (37, 40, 56, 57, 100, 3, 1, 1, True),
@@ -341,11 +349,17 @@ DIRECT_CASES = [
     (70, 100, 28, 27, 90, 3, 1, 1, False),
     (46, 64, 33, 29, 96, 3, 1, 1, True),
 ]
+STAGED_CASES = [
+    (128, 128, 32, 32, 64, 3, 1, 1, False),  # items that end with the image, over 9 k-steps
+    (130, 100, 32, 32, 60, 3, 1, 1, False),  # a last k-step of one word, ragged channels, an odd number of items
+    (2048, 64, 16, 16, 32, 3, 2, 1, False),  # 4096 tiles; stride 2, whole images
+    (128, 64, 33, 31, 96, 3, 2, 1, True),    # the same, ragged items and channels
+]
 
 
 @pytest.mark.parametrize("ab, wb", [(1, 1), (2, 1), (2, 2), (1, 3)])
-@pytest.mark.parametrize("case", DIRECT_CASES)
-def test_unstaged_form(dev, case, ab, wb):
+@pytest.mark.parametrize("case, cfg", [(c, 3) for c in DIRECT_CASES] + [(c, 1) for c in STAGED_CASES])
+def test_store_overlapped_forms(dev, case, cfg, ab, wb):
     n, cin, h, w, cout, k, s, p, packs = case
     g = synth.generator(39 + n + cin)
     x = _x(40 + n, (n, cin, h, w))
@@ -361,10 +375,13 @@ def test_unstaged_form(dev, case, ab, wb):
     z = oracle.epi_bn(acc, kk.numpy(), bb.numpy(), shift)
     geo = (n, cin, h, w, cout, k, s, p, ab, wb)
     algo = q.ALGO_MFMA_FP4
-    assert q.kernel_name(*geo, algo=algo) == f"conv_mfma_pp_kernel<1, {ab}, 1, 0>"
-    name = q.kernel_name(*geo, mode=q.EPI_BN_PACK, out_bits=ab, packed_out=True, algo=algo)
-    assert (name == f"conv_mfma_pp_kernel<1, {ab}, 1, {ab}>") == packs, name
-    out, _ = q.conv(act, wq, *geo, algo=algo)
+    name, packed = f"conv_mfma_pp_kernel<1, {ab}, {cfg}, 0>", f"conv_mfma_pp_kernel<1, {ab}, {cfg}, {ab}>"
+    assert q.kernel_name(*geo, algo=algo) == name
+    assert q.kernel_name(*geo, mode=q.EPI_BN_F32, flags=q.EPI_RESIDUAL, out_bits=ab, packed_out=True, algo=algo) == packed
+    alone = q.kernel_name(*geo, mode=q.EPI_BN_PACK, out_bits=ab, packed_out=True, algo=algo)
+    assert (alone == packed) == packs, alone
+    (out, _), ran = _launched(lambda: q.conv(act, wq, *geo, algo=algo))
+    assert ran == [name]
     np.testing.assert_array_equal(out.cpu().numpy(), acc)
     out, _ = q.conv(act, wq, *geo, mode=q.EPI_SCALE_F32, scale=sc, algo=algo)
     np.testing.assert_array_equal(out.cpu().numpy(), oracle.epi_scale(acc, osc, shift))
@@ -387,17 +404,9 @@ def test_unstaged_form(dev, case, ab, wb):
                                       oracle.quantize(oracle.hardtanh(zr), ob))
 
 
-def _launched(fn):
-    """What fn returns, and the names of the library's kernels that it launched."""
-    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
-        r = fn()
-        torch.cuda.synchronize()
-    return r, [re.sub(r"^void qc::mfma::|\(qc::mfma::.*$", "", e.key) for e in prof.key_averages() if "qc::" in e.key]
-
-
 # A stride-2 layer of wide rows: the input tile of the 256-pixel shapes does not
 # fit from 147 columns on, and no kernel that is then not launched is named
-@pytest.mark.parametrize("w, kernel", [(146, "conv_mfma_pp_kernel<1, 2, 1, "), (147, "conv_mfma_kernel<1, 2, 2, 1>"),
+@pytest.mark.parametrize("w, kernel", [(146, "conv_mfma_pp_kernel<1, 2, 3, "), (147, "conv_mfma_kernel<1, 2, 2, 1>"),
                                        (160, "conv_mfma_kernel<1, 2, 2, 1>")])
 def test_wide_rows(dev, w, kernel):
     n, c = 16, 64
