@@ -1842,18 +1842,37 @@ __device__ __forceinline__ void pp_body(const MfmaArgs& m) {
   }
 }
 
-// The unstaged form of the same layers (direct_body, above).
+// The unstaged form of the same layers (direct_body, above).  A wave's two pixel
+// tiles of the same channels come one after the other, so that the cache lines
+// their runs share (planes that are not whole runs of 128 bytes) are still in L1:
+// 64 -> 64, 33 x 33, batch 196, with residual and packed copy 36.7 -> 32.6 us.
+// The residual values of a tile are loaded before the stores of the one before
+// it, which they would else wait for (38.8 -> 36.8 there).
 template <int PA, int OB>
 __device__ __forceinline__ void unstaged(const MfmaArgs& m) {
   const ConvArgs& a = m.c;
   direct_body<PA, 2>(m, [&](const v16f (&acc)[2][2], int T0, int co, const float* prm, int lane)
                             __attribute__((always_inline)) {
+    if (a.mode == QCONV_EPI_BN_F32 && a.residual_on) {
+      float r[2][16];
+      swap_res_load(m, 0, 0, T0, co, lane, r[0]);
+      Unroll<0, 4>::run([&](auto TT) __attribute__((always_inline)) {
+        constexpr int t = decltype(TT)::value, u = t + 1;
+        if constexpr (u < 4) {
+          if (co + 32 * (u / 2) < a.cout) swap_res_load(m, 0, 0, T0 + u % 2, co + 32 * (u / 2), lane, r[u & 1]);
+        }
+        if (co + 32 * (t / 2) < a.cout)
+          tile_epilogue_swap<K_BNF32, 1, OB, true, false>(m, acc[t % 2][t / 2], 0, 0, T0 + t % 2, co + 32 * (t / 2), co,
+                                                          prm, lane, &r[t & 1]);
+      });
+      return;
+    }
     Unroll<0, 4>::run([&](auto TT) __attribute__((always_inline)) {
       constexpr int t = decltype(TT)::value;
-      const int co32 = co + 32 * (t % 2);
+      const int co32 = co + 32 * (t / 2);
       if (co32 >= a.cout) return;  // uniform
-      const v16f& A = acc[t / 2][t % 2];
-      const int T = T0 + t / 2;
+      const v16f& A = acc[t % 2][t / 2];
+      const int T = T0 + t % 2;
       if (a.mode == QCONV_EPI_INT32) {
         tile_epilogue_swap<K_INT32, 0, 0, true>(m, A, 0, 0, T, co32, co, prm, lane);
       } else if (a.mode == QCONV_EPI_SCALE_F32) {
@@ -1861,7 +1880,7 @@ __device__ __forceinline__ void unstaged(const MfmaArgs& m) {
       } else if (a.mode == QCONV_EPI_BN_PACK) {
         if constexpr (OB > 0) tile_epilogue_swap<K_PACK, 0, OB, true>(m, A, 0, 0, T, co32, co, prm, lane);
       } else {
-        tile_epilogue_swap<K_BNF32, 2, OB, true>(m, A, 0, 0, T, co32, co, prm, lane);
+        tile_epilogue_swap<K_BNF32, 0, OB, true>(m, A, 0, 0, T, co32, co, prm, lane);
       }
     });
   });

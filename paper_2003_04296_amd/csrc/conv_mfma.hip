@@ -191,6 +191,19 @@ bool direct_applies(const ConvArgs& a, MfmaArgs* m) {
   const bool full = upi % 256 == 0 || (upi < 256 && 256 % upi == 0);
   if (tiles <= 4096 || a.cout > 256) return false;
   if (steps > 9 && (steps > 18 || full || a.mode == QCONV_EPI_BN_PACK)) return false;
+  if (a.residual_on && upi % 16 != 0) {
+    // every 128-byte run of the output and of the residual lies in two cache
+    // lines: the staged form where its items of 256 pixels x 64 channels fill
+    // its rounds well (residual and packed copy, staged / unstaged: 64 -> 64, 33
+    // x 33, 1200 items 37.5 / 38.7 us, 2500 81.8 / 87.2; 30 x 30, 2500 90.4 /
+    // 90.1; 128 -> 64, 33 x 33, 2500 86.6 / 96.4, 30 x 30 93.1 / 99.7; 128 -> 128,
+    // 33 x 33, 860 33.5 / 31.3, 980 34.6 / 37.7, 1200, in 128-channel items,
+    // 51.3 / 41.9; 30 x 30, 1008 38.4 / 35.6; 64 -> 256, 25 x 25, 972 34.0 / 36.6)
+    const int64_t items = (upi >= 256 ? a.n * ((upi + 255) / 256) : (units + 255) / 256) * ceil_div(a.cout, 64);
+    const bool odd = upi % 4 != 0, deep = steps > 9;
+    if (a.cout <= 64 ? (odd && items > 1536) || (deep && items > 2048) : odd && items > 896 && items <= 1024)
+      return false;
+  }
   const int64_t wxb = (int64_t)a.kh * a.kw * ksteps * a.cop * 32;
   const int64_t ab = (int64_t)a.n * a.h * a.w * a.cw * act_words(a.a_bits) * 4;
   const int64_t ob = units * a.cout * 4;

@@ -404,6 +404,32 @@ def test_store_overlapped_forms(dev, case, cfg, ab, wb):
                                       oracle.quantize(oracle.hardtanh(zr), ob))
 
 
+# Residual layers whose planes are not whole runs of 64 bytes: the form on both
+# sides of each limit (items of 256 pixels x 64 channels; planes of a multiple of four
+# pixels and not, up to 9 k-steps and more)
+@pytest.mark.parametrize("n, cin, h, w, cout, cfg", [
+    (512, 64, 25, 25, 64, 3), (513, 64, 25, 25, 64, 1), (513, 64, 25, 28, 64, 3), (513, 64, 26, 26, 64, 3),
+    (513, 128, 25, 25, 64, 1), (512, 128, 30, 30, 64, 3), (513, 128, 30, 30, 64, 1), (513, 128, 28, 28, 64, 3),
+    (149, 100, 25, 23, 90, 3), (150, 100, 25, 23, 90, 1), (170, 100, 25, 23, 90, 1), (171, 100, 25, 23, 90, 3),
+    (150, 64, 25, 23, 90, 1), (150, 100, 26, 22, 90, 3)])
+def test_residual_form(dev, n, cin, h, w, cout, cfg):
+    geo = (n, cin, h, w, cout, 3, 1, 1, 2, 2)
+    kw = dict(mode=q.EPI_BN_F32, flags=q.EPI_RESIDUAL, out_bits=2)
+    assert q.kernel_name(*geo, packed_out=True, **kw) == f"conv_mfma_pp_kernel<1, 2, {cfg}, 2>"
+    assert q.kernel_name(*geo, mode=q.EPI_BN_F32) == "conv_mfma_pp_kernel<1, 2, 3, 0>"
+    g = torch.Generator(device=dev).manual_seed(54)
+    x = torch.randn((n, cin, h, w), generator=g, device=dev)
+    res = torch.randn((n, cout, h, w), generator=g, device=dev)
+    wq, _ = q.pack_weight(torch.randn((cout, cin, 3, 3), generator=g, device=dev), 2)
+    bn = dict(bn_k=torch.rand(cout, generator=g, device=dev) * 0.05, bn_b=torch.randn(cout, generator=g, device=dev))
+    outp = torch.zeros(q.packed_act_words(n, cout, h, w, 2), dtype=torch.int32, device=dev)
+    out, _ = q.conv(q.pack_act(x, 2), wq, *geo, residual=res, out_packed=outp, **kw, **bn)
+    assert torch.equal(outp, q.pack_act(out, 2))  # (|z| <= 1 or not: the threshold is below 1)
+    for i0, m in ((0, 2), (n - 2, 2)):  # the first and the last images alone, on another kernel
+        part, _ = q.conv(q.pack_act(x[i0:i0 + m].contiguous(), 2), wq, m, *geo[1:], mode=q.EPI_BN_F32, **bn)
+        assert torch.equal(out[i0:i0 + m], part + res[i0:i0 + m])
+
+
 # A stride-2 layer of wide rows: the input tile of the 256-pixel shapes does not
 # fit from 147 columns on, and no kernel that is then not launched is named
 @pytest.mark.parametrize("w, kernel", [(146, "conv_mfma_pp_kernel<1, 2, 3, "), (147, "conv_mfma_kernel<1, 2, 2, 1>"),
