@@ -37,9 +37,9 @@ namespace mfma {
 // of the steps past a wave's range costs more than a second round saves)
 constexpr int LAT_D = 5;
 
-// One piece of the epilogue: four rows (or one window) of 32 channels per
-// half-wave.  s: the summed accumulators; T: the tile's index in units of 32
-// rows; kv, bv: this lane's channel parameters; rv: residual values.
+// The packed words of one piece of the epilogue: four rows (or one window) of 32
+// channels per half-wave.  z: this lane's output values; u0: the tile's first
+// unit; q: the piece; co32: its first channel; total: units of the layer.
 template <int POOL, int OB>
 __device__ __forceinline__ void lat_pack(const MfmaArgs& m, const float (&z)[4], int u0, int q, int co32, int total,
                                          int lane) {
@@ -81,36 +81,30 @@ __device__ __forceinline__ void lat_pack(const MfmaArgs& m, const float (&z)[4],
 
 template <int PA, int NT, int SK, int POOL>
 __global__ __launch_bounds__(64 * SK) void conv_mfma_lat_kernel(const MfmaArgs m) {
-  constexpr int MT = 1;  // two M-tiles a block measured slower at every size
-  constexpr int PIECES = MT * NT * 4, PPW = (PIECES + SK - 1) / SK, D = LAT_D;
-  constexpr int TU = POOL ? 8 : 32;  // units per M-tile
+  // one tile of 32 rows a block: two measured slower at every size
+  constexpr int PIECES = NT * 4, PPW = (PIECES + SK - 1) / SK, D = LAT_D;
+  constexpr int TU = POOL ? 8 : 32;  // units per block
   extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
   const ConvArgs& a = m.c;
   const int tid = threadIdx.x, lane = tid & 63, wk = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, r32 = lane & 31;
   const int pt = (int)blockIdx.x / m.tiles_co;
   const int co_blk = ((int)blockIdx.x - pt * m.tiles_co) * (32 * NT);
-  const int T0 = pt * MT;
   const int total = a.n * m.upi;
 
-  // the pixel of each M-tile row: byte offset of its first tap's word (this
+  // the pixel of this lane's row: byte offset of its first tap's word (this
   // lane's k-half; may lie before the tensor) and the taps inside the image
   const int apix = a.cw * PA * 4;  // bytes per pixel
-  int base[MT];
-  uint32_t rmask[MT], cmask[MT];
-#pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int unit = POOL ? 8 * (T0 + i) + 4 * ((r32 >> 2) & 1) + (r32 >> 3) : 32 * (T0 + i) + r32;
-    const int img = (int)fdiv((uint32_t)unit, m.fd_upi);
-    const int uu = unit - img * m.upi;
-    const int uy = (int)fdiv((uint32_t)uu, m.fd_uw);
-    const int ux = uu - uy * m.uw;
-    const int iy = (POOL ? 2 * uy + ((r32 >> 1) & 1) : uy) * a.stride - a.pad;
-    const int ix = (POOL ? 2 * ux + (r32 & 1) : ux) * a.stride - a.pad;
-    base[i] = ((img * a.h + iy) * a.w + ix) * apix + g * (PA * 4);
-    rmask[i] = unit < total ? tap_mask(iy, a.h, a.kh) : 0u;
-    cmask[i] = tap_mask(ix, a.w, a.kw);
-  }
+  const int unit = POOL ? 8 * pt + 4 * ((r32 >> 2) & 1) + (r32 >> 3) : 32 * pt + r32;
+  const int uimg = (int)fdiv((uint32_t)unit, m.fd_upi);
+  const int uu = unit - uimg * m.upi;
+  const int uy = (int)fdiv((uint32_t)uu, m.fd_uw);
+  const int ux = uu - uy * m.uw;
+  const int iy = (POOL ? 2 * uy + ((r32 >> 1) & 1) : uy) * a.stride - a.pad;
+  const int ix = (POOL ? 2 * ux + (r32 & 1) : ux) * a.stride - a.pad;
+  const int base = ((uimg * a.h + iy) * a.w + ix) * apix + g * (PA * 4);
+  const uint32_t rmask = unit < total ? tap_mask(iy, a.h, a.kh) : 0u;
+  const uint32_t cmask = tap_mask(ix, a.w, a.kw);
   const __amdgpu_buffer_rsrc_t arsrc =
       __builtin_amdgcn_make_buffer_rsrc((void*)a.act, (short)0, m.act_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t brsrc =
@@ -124,21 +118,18 @@ __global__ __launch_bounds__(64 * SK) void conv_mfma_lat_kernel(const MfmaArgs m
   int step = sbeg;
   const int tap0 = sbeg / m.ksteps;
   int ks = sbeg - tap0 * m.ksteps, ky = tap0 / a.kw, kx = tap0 - (tap0 / a.kw) * a.kw;
-  int voff[MT];
+  int voff;
   auto tap_offsets = [&]() __attribute__((always_inline)) {
     const int to = (ky * a.w + kx) * apix;
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-      voff[i] = ((rmask[i] >> ky) & (cmask[i] >> kx) & 1u) ? base[i] + to : OFF_NONE;
+    voff = ((rmask >> ky) & (cmask >> kx) & 1u) ? base + to : OFF_NONE;
   };
   tap_offsets();
-  uint32_t ra[D][MT][PA];
+  uint32_t ra[D][PA];
   v4i rb[D][NT];
   auto issue = [&](auto DD) __attribute__((always_inline)) {
     constexpr int d = decltype(DD)::value;
     const int ao = ks * (2 * PA * 4), bo = step * bstride;
-#pragma unroll
-    for (int i = 0; i < MT; ++i) load_words<PA>(arsrc, voff[i], ao, ra[d][i]);
+    load_words<PA>(arsrc, voff, ao, ra[d]);
 #pragma unroll
     for (int j = 0; j < NT; ++j)
       rb[d][j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(brsrc, bvoff + j * 1024, bo, 0));
@@ -152,23 +143,18 @@ __global__ __launch_bounds__(64 * SK) void conv_mfma_lat_kernel(const MfmaArgs m
       tap_offsets();
     }
   };
-  v16f acc[MT][NT];
+  v16f acc[NT];
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
+  for (int j = 0; j < NT; ++j)
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    for (int v = 0; v < 16; ++v) acc[j][v] = 0.0f;
   auto consume = [&](auto DD) __attribute__((always_inline)) {
     constexpr int d = decltype(DD)::value;
+    uint32_t o[4];
+    expand_fp4_word<PA>(ra[d], 0xFFFFFFFFu, o);
+    const v4i A = {(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      uint32_t o[4];
-      expand_fp4_word<PA>(ra[d][i], 0xFFFFFFFFu, o);
-      const v4i A = {(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
-#pragma unroll
-      for (int j = 0; j < NT; ++j) acc[i][j] = mfma<OP_FP4>(A, rb[d][j], acc[i][j]);
-    }
+    for (int j = 0; j < NT; ++j) acc[j] = mfma<OP_FP4>(A, rb[d][j], acc[j]);
   };
   int left = send - sbeg;
   Unroll<0, D>::run([&](auto dd) {
@@ -190,13 +176,13 @@ __global__ __launch_bounds__(64 * SK) void conv_mfma_lat_kernel(const MfmaArgs m
   int oo[PPW][NV];  // byte offsets of the outputs
 #pragma unroll
   for (int k = 0; k < PPW; ++k) {
-    const int pc = wk + SK * k;  // piece: tile pc / 4, rows pc % 4
-    const int ti = (pc >> 2) / NT, tj = (pc >> 2) - ti * NT, q = pc & 3;
+    const int pc = wk + SK * k;  // piece: channel tile pc / 4, rows pc % 4
+    const int tj = pc >> 2, q = pc & 3;
     const int co = co_blk + 32 * tj + r32;
     const int cvo = co < a.cout ? co * 4 : OFF_NONE;
     kv[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(krsrc, cvo, 0, 0));
     bv[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(prsrc, cvo, 0, 0));
-    const int u = (T0 + ti) * TU + (POOL ? q + 4 * g : 8 * q + 4 * g);
+    const int u = pt * TU + (POOL ? q + 4 * g : 8 * q + 4 * g);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       oo[k][i] = OFF_NONE;
@@ -228,20 +214,18 @@ __global__ __launch_bounds__(64 * SK) void conv_mfma_lat_kernel(const MfmaArgs m
   typedef float e4 __attribute__((ext_vector_type(4)));
   e4* red = reinterpret_cast<e4*>(lds_raw);
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
+  for (int j = 0; j < NT; ++j)
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const e4 t = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-        red[(((i * NT + j) * 4 + q) * SK + wk) * 64 + lane] = t;
-      }
+    for (int q = 0; q < 4; ++q) {
+      const e4 t = {acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+      red[((j * 4 + q) * SK + wk) * 64 + lane] = t;
+    }
   lds_barrier();
 #pragma unroll
   for (int k = 0; k < PPW; ++k) {
     const int pc = wk + SK * k;
     if (pc >= PIECES) break;  // uniform
-    const int ti = (pc >> 2) / NT, tj = (pc >> 2) - ti * NT, q = pc & 3;
+    const int tj = pc >> 2, q = pc & 3;
     const int co32 = co_blk + 32 * tj;
     if (co32 >= a.cout) continue;  // uniform
     e4 s = red[(pc * SK) * 64 + lane];
@@ -276,7 +260,7 @@ __global__ __launch_bounds__(64 * SK) void conv_mfma_lat_kernel(const MfmaArgs m
       }
     }
     if (a.out_packed) {
-      const int u0 = (T0 + ti) * TU;
+      const int u0 = pt * TU;
       if (a.out_bits == 1) lat_pack<POOL, 1>(m, z, u0, q, co32, total, lane);
       else if (a.out_bits == 2) lat_pack<POOL, 2>(m, z, u0, q, co32, total, lane);
       else lat_pack<POOL, 3>(m, z, u0, q, co32, total, lane);
