@@ -177,10 +177,18 @@ int pick_cfg_base(const ConvArgs& a) {
 // (direct_body), and its arguments.  Up to 9 k-steps (3 x 3 over 64 channels)
 // it is the faster one at every map size measured; up to 18 where 256-pixel
 // items leave part of an item past an image's end (28 x 28 batch 256: 38.9 ->
-// 33.1 us; 32 x 32, full items, batch 128: 22.7 us staged, 23.5 unstaged), but
-// not for a packed output alone, which the base kernel runs; past that the
-// staged forms win (256 x 14 x 14 batch 128, 36 steps: 20.3 us staged, 20.7).
-// Over 4096 tiles of 32 x 32 (16 a CU); with fewer the smaller shapes serve.
+// 33.1 us; 32 x 32, full items, batch 128: 22.7 us staged, 23.5 unstaged); past
+// that the staged forms win (256 x 14 x 14 batch 128, 36 steps: 20.3 us staged,
+// 20.7).
+// Two of the limits are not where the sides meet, but where the form was taken
+// up.  Packed outputs alone of 10 to 18 steps stay on the base kernel (128 ->
+// 128, 28 x 28, batch 64 13.2 us, unstaged 10.6; batch 256 31.4, 26.7; 96 -> 96,
+// batch 100 21.5, 12.8).  Layers of up to 4096 tiles of 32 x 32 stay on the
+// smaller shapes: with residual and packed copy 64 x 56 x 56, 686 to 980 tiles
+// 9.4 to 9.9 us (unstaged 9.2, 9.5), 1470 15.5 (10.1), 1960 17.2 (10.6); 64 x 28 x
+// 28, 4018 tiles 21.5 (10.7); but 64 x 32 x 32, 1984 tiles 9.6 (10.5).
+// So is a bound: maps and batches whose fast divisions need 64 bits (56 x 56 past
+// 436 images) take the staged forms.
 bool direct_applies(const ConvArgs& a, MfmaArgs* m) {
   if (a.mfma_op != OP_FP4 || a.a_bits > 2 || a.pool || a.stride > 2 || a.kh > 16 || a.kw > 16 || a.n < 1) return false;
   if (a.out_packed && ((a.mode != QCONV_EPI_BN_F32 && a.mode != QCONV_EPI_BN_PACK) || a.out_bits != a.a_bits))

@@ -28,11 +28,13 @@ __device__ __forceinline__ uint32_t chan_mask(int remaining) {
 // `group` words of `sub` runs, one wave per unit, in LDS and writes each
 // pixel's as one run; where they are all of its words the block's whole output
 // is one run.
-// Bound by reading fp32 from HBM; measured on 1 / 2 / 3 bits with inputs not
-// in cache: 256 x 64 x 56 x 56 37.7 / 40.6 / 45.0 us (5.1-5.6 TB/s), 256 x 512
-// x 8 x 8 8.3 / 8.7 / 9.8 us, where waves that looped over whole pixel runs
-// of one image and branched per 3-bit compare took 37.8 / 40.7 / 120.6 and
-// 12.9 / 14.3 / 63.9 us.  Two or four pixels per lane (8- and 16-byte loads)
+// Bound by reading fp32 from HBM.  Inputs in cache / not, 2 bits: 256 x 64 x 56 x
+// 56 32.9 / 42.2 us, 256 x 512 x 8 x 8 5.4 / 9.1, where waves that looped over
+// whole pixel runs of one image took 33.1 / 42.7 and 8.3 / 15.4; 900 x 300 x 9 x
+// 9 at 3 bits 21.1 / 25.0, where they branched per compare and took 43.5 / 58.8.
+// In a loop whose convolution has just left 134 or 205 MB of writes, whose
+// write-back shares HBM, the first at 3 bits takes 58.6 us and 256 x 128 x 32 x
+// 32 at 2 bits 28.9 (22.7 / 28.6).  Two or four pixels per lane (8- and 16-byte loads)
 // and 8 or 32 channels in flight measured the same or slower.
 // Compares are gathered from the highest channel down, word = 2 word + bit
 // (one v_addc per compare).  With t0 >= 0, x > t0 is the sign of a nonzero
@@ -212,7 +214,7 @@ __global__ __launch_bounds__(256) void pack_act_f16_kernel(const float* __restri
 // images) x `group` words, one wave per word of 64 pixels with all its channels'
 // loads in flight, and writes each pixel's words as one run.  The direct kernel
 // above stores 16 bytes per lane 64 bytes and more apart.  Bound by HBM.
-// Inputs in cache / not, against the direct kernel: 256 x 128 x 32 x 32 30.1 /
+// In the loop of an a16w1 layer 256 x 128 x 32 x 32 takes 42.4 us; inputs in cache / not, against the direct kernel: 256 x 128 x 32 x 32 30.1 /
 // 39.3 us (34.2 / 46.6), 256 x 64 x 56 x 56 52.2 / 57.9 (61.3 / 67.6); 4 x 128 x
 // 32 x 32, too few blocks, 3.7 in cache (3.0).
 __global__ __launch_bounds__(512) void pack_act_f16_lds_kernel(const float* __restrict__ x, int c, int hw, int cwn,
