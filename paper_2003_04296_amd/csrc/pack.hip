@@ -214,9 +214,10 @@ __global__ __launch_bounds__(256) void pack_act_f16_kernel(const float* __restri
 // images) x `group` words, one wave per word of 64 pixels with all its channels'
 // loads in flight, and writes each pixel's words as one run.  The direct kernel
 // above stores 16 bytes per lane 64 bytes and more apart.  Bound by HBM.
-// In the loop of an a16w1 layer 256 x 128 x 32 x 32 takes 42.4 us; inputs in cache / not, against the direct kernel: 256 x 128 x 32 x 32 30.1 /
-// 39.3 us (34.2 / 46.6), 256 x 64 x 56 x 56 52.2 / 57.9 (61.3 / 67.6); 4 x 128 x
-// 32 x 32, too few blocks, 3.7 in cache (3.0).
+// In the loop of an a16w1 layer 256 x 128 x 32 x 32 takes 42.4 us; inputs in
+// cache / not, against the direct kernel, it takes 30.1 / 39.3 us (34.2 / 46.6),
+// 256 x 64 x 56 x 56 52.2 / 57.9 (61.3 / 67.6); 4 x 128 x 32 x 32, too few blocks,
+// 3.7 in cache (3.0).
 __global__ __launch_bounds__(512) void pack_act_f16_lds_kernel(const float* __restrict__ x, int c, int hw, int cwn,
                                                                int groups, int group, int sub, int npix,
                                                                uint4* __restrict__ out) {
