@@ -313,12 +313,11 @@ bool use_pp(const MfmaArgs& m, int cfg, int cus) {
   return true;
 }
 
-// The kernel that runs a layer (m->form) with its block shape and arguments,
-// for the launch and for its name; false: none serves it.  (The unstaged form
-// and the few-tiles kernel have no input tile in LDS, but are not asked for more
-// layers than the kernels that do: the tile of the 64-channel shape, for the
-// few-tiles kernel of any shape, has to fit.)
-bool choose(const ConvArgs& a, int* cfg, MfmaArgs* m) {
+// The block shape that runs a layer and its arguments; false: none serves it.
+// (The unstaged form and the few-tiles kernel have no input tile in LDS, but are
+// not asked for more layers than the kernels that do: the tile of the 64-channel
+// shape, for the few-tiles kernel of any shape, has to fit.)
+bool fits(const ConvArgs& a, int* cfg, MfmaArgs* m) {
   if (a.stride > 2 || a.n < 1) return false;
   MfmaArgs d;
   if (direct_applies(a, &d) && plan(a, 1, m)) {
@@ -327,10 +326,17 @@ bool choose(const ConvArgs& a, int* cfg, MfmaArgs* m) {
     return true;
   }
   *cfg = pick_cfg(a);
-  if (!plan(a, *cfg, m)) return false;
-  m->form = lat_applies(a) ? FORM_LAT : (use_pp(*m, *cfg, device_cus()) ? FORM_PP : FORM_BASE);
+  return plan(a, *cfg, m);
+}
+
+// The kernel that runs it (m->form) as well, for the launch and for its name.
+bool choose(const ConvArgs& a, int* cfg, MfmaArgs* m) {
+  if (!fits(a, cfg, m)) return false;
+  if (*cfg != CFG_DIRECT)
+    m->form = lat_applies(a) ? FORM_LAT : (use_pp(*m, *cfg, device_cus()) ? FORM_PP : FORM_BASE);
   return true;
 }
+
 }  // namespace mfma
 
 using namespace mfma;
@@ -340,7 +346,7 @@ bool mfma_is_small(const ConvArgs& a) { return lat_beats_xnor(a); }
 bool mfma_supports(const ConvArgs& a) {
   int cfg;
   MfmaArgs m;
-  return choose(a, &cfg, &m);
+  return fits(a, &cfg, &m);
 }
 
 int mfma_kernel_name(const ConvArgs& a, char* buf, int len) {
